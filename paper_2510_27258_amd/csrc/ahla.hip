@@ -451,7 +451,7 @@ hipError_t run_ahla(const Fwd& f, char* ws, int P, int cps, hipStream_t s) {
   if (P > 1 || f.normalized) {
     prof_start("ahla_carry", s);
     HLA_LAUNCH((k_carry<D, D>), dim3((D * D / 8 + D + 255) / 256, BH), dim3(256), 0, s, segs,
-                       (const float*)nullptr, carry, P, 1.f);
+                       0, carry, P, 1.f);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     using FC = FixCfg<C, D, D>;

@@ -14,9 +14,9 @@
 //      its record;
 //   3. k_carry / k_fix: running sums of the brackets are the carries;
 //      out_t += q_t^T Phi_c (and the division when normalised).
-// With an initial state, k_init_convert converts it to the (S, C, m, Phi, eta)
-// form first; k_total sums all records into the final state when a caller
-// asks for it.  k_moments, k_carry and k_fix live in fused_tiles.h.
+// With a decode state, k_state_to_phi converts it to the (S, C, m, Phi, eta)
+// form first; k_rec_sum sums all records and k_phi_to_state converts the sum
+// back into the state.  k_moments, k_carry and k_fix live in fused_tiles.h.
 // At d = dv = 128 without states the forward takes the two-pass plan of
 // fused_ws.h instead (run_ws): segment 0's output walk beside the summary
 // walks of the later segments, the brackets, then the other segments' output
@@ -51,6 +51,7 @@
 #include "fused.h"
 #include "fused_tiles.h"
 #include "fused_ws.h"
+#include "mfma16.h"
 #include "profile.h"
 
 namespace hla {
@@ -103,165 +104,126 @@ struct Cfg {
 // when a final state is wanted) and, after its walk, its bracket.  Slot nseg
 // holds the initial state converted to this form (written only when there is
 // one).  Carries and the total are plain sums of these records (the Phi form
-// of Eq. (semidirect)); the total is converted back to G, h once (k_total).
+// of Eq. (semidirect)); the total is converted back to G, h once (k_phi_to_state).
 
-// out[a][b] = z * Z[a][b] + sum_a' X[a][a'] Y[a'][b] for the thread's TI x TI
-// register blocks; XT = X^T ([D][D+4]) and Y ([D][DV]) in LDS, Z and out in
-// global memory with row stride DV (out may alias Z).
-template <int D, int DV>
-__device__ __forceinline__ void xy_plus(const float* XT, const float* Y, const float* Z, float z, float* out) {
-  constexpr int TI = (D >= 128 || DV >= 128) ? 8 : 4, ldT = D + 4;
-  constexpr int NBJ = DV / TI, NB = (D / TI) * NBJ;
-  for (int blk = threadIdx.x; blk < NB; blk += blockDim.x) {
-    const int a0 = TI * (blk / NBJ), b0 = TI * (blk % NBJ);
-    float o[TI][TI] = {};
-#pragma unroll 4
-    for (int ap = 0; ap < D; ++ap) {
-      float xv[TI], yv[TI];
+// Rows r0 .. r0+15 of S C - Z and S m - z for one head, written to dst, dstv:
+// one wave per 16 x 16 tile on v_mfma_f32_16x16x4_f32 (fp32 products and
+// sums), S's rows in LDS (Sr [16][D+17], staged by stage() after the tile's
+// loads of C and Z from global memory have been issued).
+template <int D, int DV, typename ST>
+__device__ __forceinline__ void cross_rows(const float* Sr, int r0, const float* C, const float* m, const float* Z,
+                                           const float* z, float* dst, float* dstv, ST stage) {
+  constexpr int ld = D + 17;
+  const int tid = threadIdx.x, c0 = (tid >> 6) * 16, nn = tid & 15, g = (tid >> 4) & 3;
+  float y[D / 4], zt[4];
 #pragma unroll
-      for (int i = 0; i < TI; i += 4) {
-        const float4 x4 = *reinterpret_cast<const float4*>(&XT[ap * ldT + a0 + i]);
-        const float4 y4 = *reinterpret_cast<const float4*>(&Y[ap * DV + b0 + i]);
-        xv[i] = x4.x; xv[i + 1] = x4.y; xv[i + 2] = x4.z; xv[i + 3] = x4.w;
-        yv[i] = y4.x; yv[i + 1] = y4.y; yv[i + 2] = y4.z; yv[i + 3] = y4.w;
-      }
+  for (int s = 0; s < D / 4; ++s) y[s] = C[(size_t)(4 * s + g) * DV + c0 + nn];
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
+  for (int i = 0; i < 4; ++i) zt[i] = Z[(size_t)(r0 + 4 * g + i) * DV + c0 + nn];
+  stage();
+  __syncthreads();
+  f32x4c acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < TI; ++j) o[i][j] += xv[i] * yv[j];
-    }
+  for (int s = 0; s < D / 4; ++s) acc = mfma4(Sr[nn * ld + 4 * s + g], y[s], acc);
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TI; j += 4) {
-        const size_t off = (size_t)(a0 + i) * DV + b0 + j;
-        const float4 z4 = *reinterpret_cast<const float4*>(Z + off);
-        *reinterpret_cast<float4*>(out + off) =
-            make_float4(o[i][j] + z * z4.x, o[i][j + 1] + z * z4.y, o[i][j + 2] + z * z4.z, o[i][j + 3] + z * z4.w);
-      }
-  }
-}
-
-// out[a] = z * zv[a] + sum_a' X[a][a'] y[a'] for a = threadIdx.x < D.
-template <int D>
-__device__ __forceinline__ void xv_plus(const float* XT, const float* y, const float* zv, float z, float* out) {
-  const int a = threadIdx.x;
-  if (a >= D) return;
-  float acc = 0.f;
+  for (int i = 0; i < 4; ++i) dst[(size_t)(r0 + 4 * g + i) * DV + c0 + nn] = acc[i] - zt[i];
+  // four lanes per row of S m, in the first wave
+  if (tid < 64) {
+    const int row = tid >> 2, p = tid & 3;
+    float x = 0.f;
 #pragma unroll 8
-  for (int ap = 0; ap < D; ++ap) acc += XT[ap * (D + 4) + a] * y[ap];
-  out[a] = acc + z * zv[a];
-}
-
-// Stage X^T (X from float4 registers, row-major [D][D] split as element
-// 4 * (tid + 256 r)), Y ([D][DV] float4 registers) and y into LDS.
-template <int D, int DV>
-__device__ __forceinline__ void stage_xy(float* XT, float* Y, float* y, const float4* xs, const float4* ys, float yv) {
-  constexpr int nS4 = D * D / 4 / 256, nC4 = D * DV / 4 / 256, ldT = D + 4;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int r = 0; r < nS4; ++r) {
-    const int e4 = tid + 256 * r, a = (4 * e4) / D, ap = (4 * e4) % D;
-    XT[(ap + 0) * ldT + a] = xs[r].x;
-    XT[(ap + 1) * ldT + a] = xs[r].y;
-    XT[(ap + 2) * ldT + a] = xs[r].z;
-    XT[(ap + 3) * ldT + a] = xs[r].w;
+    for (int j = p; j < D; j += 4) x += Sr[row * ld + j] * m[j];
+    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 2);
+    if (p == 0) dstv[r0 + row] = x - z[r0 + row];
   }
-#pragma unroll
-  for (int r = 0; r < nC4; ++r) reinterpret_cast<float4*>(Y)[tid + 256 * r] = ys[r];
-  if (tid < D) y[tid] = yv;
 }
 
-__device__ __forceinline__ void add4(float4& a, const float4& b) {
-  a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-}
-
-// k_init_convert: grid (1, BH), 256 threads.  Writes the initial state of
-// every head into slot nseg of its records in the (S, C, m, Phi, eta) form:
-// (S, C, m, S C - G, S m - h).
+// Between a decode state (packed record S | C | m | G | h) and a full record
+// in the (S, C, m, Phi, eta) form of the walks: Phi = S C - G, eta = S m - h
+// and back.  grid (D / 16, BH), one wave per 16-column tile, 16 rows a
+// workgroup: a workgroup per head left most of the chip idle on few heads
+// (32 heads, d = 128: one workgroup and
+// fp32 FMAs on register tiles took 36 us there and 85 us back, the row split
+// 9 and 9 us).  Each row block reads all of C, through L2.
 template <int D, int DV>
-__global__ __launch_bounds__(256) void k_init_convert(float* __restrict__ segs, const float* __restrict__ init,
-                                                      int nseg) {
-  constexpr int nS4 = D * D / 4 / 256, nC4 = D * DV / 4 / 256;
-  static_assert(D * D % 1024 == 0 && D * DV % 1024 == 0, "thread split");
-  extern __shared__ float sm[];
-  float* XT = sm;                 // [D][D+4]  S^T
-  float* Y = XT + D * (D + 4);    // [D][DV]   C
-  float* y = Y + D * DV;          // [D]       m
-  const int bh = blockIdx.y, tid = threadIdx.x;
-  const size_t F = state_floats(D, DV);
-  const float* src = init + (size_t)bh * F;
-  float* dst = segs + ((size_t)bh * (nseg + 1) + nseg) * F;
-  float4 xs[nS4], ys[nC4];
+__global__ __launch_bounds__(4 * DV) void k_state_to_phi(const float* __restrict__ state, float* __restrict__ segs,
+                                                         int nseg) {
+  constexpr int ld = D + 17, NT = 4 * DV;
+  __shared__ float Sr[16 * ld];
+  const int r0 = blockIdx.x * 16, bh = blockIdx.y, tid = threadIdx.x;
+  const float* src = state + (size_t)bh * dstate_floats(D, DV);
+  float* dst = segs + ((size_t)bh * (nseg + 1) + nseg) * state_floats(D, DV);
+  const float* C = src + packed_s_floats(D);
+  const float* m = C + D * DV;
+  auto stage = [&] {
 #pragma unroll
-  for (int r = 0; r < nS4; ++r) xs[r] = reinterpret_cast<const float4*>(src)[tid + 256 * r];
+    for (int i = 0; i < 16 * D / NT; ++i) {
+      const int e = tid + NT * i, r = r0 + e / D, j = e % D, a = min(r, j), c = max(r, j);
+      const float x = src[a < D / 2 ? a * (D + 1) + c - a : (D - 1 - a) * (D + 1) + c + 1];
+      Sr[(e / D) * ld + j] = x;
+      dst[(size_t)r * D + j] = x;
+    }
 #pragma unroll
-  for (int r = 0; r < nC4; ++r) ys[r] = reinterpret_cast<const float4*>(src + off_C(D, DV))[tid + 256 * r];
-  const float yv = tid < D ? src[off_m(D, DV) + tid] : 0.f;
-  stage_xy<D, DV>(XT, Y, y, xs, ys, yv);
-#pragma unroll
-  for (int r = 0; r < nS4; ++r) reinterpret_cast<float4*>(dst)[tid + 256 * r] = xs[r];
-#pragma unroll
-  for (int r = 0; r < nC4; ++r) reinterpret_cast<float4*>(dst + off_C(D, DV))[tid + 256 * r] = ys[r];
-  if (tid < D) dst[off_m(D, DV) + tid] = yv;
-  __syncthreads();
-  xy_plus<D, DV>(XT, Y, src + off_G(D, DV), -1.f, dst + off_G(D, DV));
-  xv_plus<D>(XT, y, src + off_h(D, DV), -1.f, dst + off_h(D, DV));
+    for (int i = 0; i < 16 * DV / NT; ++i) {
+      const size_t e = (size_t)r0 * DV + tid + NT * i;
+      dst[off_C(D, DV) + e] = C[e];
+    }
+    if (tid < 16) dst[off_m(D, DV) + r0 + tid] = m[r0 + tid];
+  };
+  cross_rows<D, DV>(Sr, r0, C, m, m + D, m + D + D * DV, dst + off_G(D, DV), dst + off_h(D, DV), stage);
 }
 
-// k_total: grid (BH), 256 threads.  The state after all nsum segments in the
-// S|C|m|G|h form: S, C, m, Phi, eta are sums over the converted initial state
-// and the brackets; then G = S C - Phi and h = S m - eta.
+// total: [BH][F] records in the (S, C, m, Phi, eta) form.
 template <int D, int DV>
-__global__ __launch_bounds__(256) void k_total(const float* __restrict__ segs, const float* __restrict__ init,
-                                               float* __restrict__ fin, int nseg, int nsum) {
-  constexpr int nS4 = D * D / 4 / 256, nC4 = D * DV / 4 / 256, ldT = D + 4;
-  extern __shared__ float sm[];
-  float* XT = sm;
-  float* Y = XT + D * ldT;
-  float* y = Y + D * DV;
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  const size_t F = state_floats(D, DV);
-  const float* base = segs + (size_t)bh * (nseg + 1) * F;
-  float* out = fin + (size_t)bh * F;
-  float4 xs[nS4], ys[nC4];
-  float yv = 0.f, ev = 0.f;
-  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+__global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict__ total, float* __restrict__ state) {
+  constexpr int ld = D + 17, NT = 4 * DV;
+  __shared__ float Sr[16 * ld];
+  const int r0 = blockIdx.x * 16, bh = blockIdx.y, tid = threadIdx.x;
+  const float* src = total + (size_t)bh * state_floats(D, DV);
+  float* dst = state + (size_t)bh * dstate_floats(D, DV);
+  float* C = dst + packed_s_floats(D);
+  float* m = C + D * DV;
+  auto stage = [&] {
 #pragma unroll
-  for (int r = 0; r < nS4; ++r) xs[r] = z4;
+    for (int i = 0; i < 16 * D / NT; ++i) {
+      const int e = tid + NT * i, r = r0 + e / D, j = e % D;
+      const float x = src[(size_t)r * D + j];
+      Sr[(e / D) * ld + j] = x;
+      if (j >= r) dst[r < D / 2 ? r * (D + 1) + j - r : (D - 1 - r) * (D + 1) + j + 1] = x;
+    }
 #pragma unroll
-  for (int r = 0; r < nC4; ++r) ys[r] = z4;
-  for (int sp = init ? -1 : 0; sp < nsum; ++sp) {
-    const float* x = base + (size_t)(sp < 0 ? nseg : sp) * F;
+    for (int i = 0; i < 16 * DV / NT; ++i) {
+      const size_t e = (size_t)r0 * DV + tid + NT * i;
+      C[e] = src[off_C(D, DV) + e];
+    }
+    if (tid < 16) m[r0 + tid] = src[off_m(D, DV) + r0 + tid];
+  };
+  cross_rows<D, DV>(Sr, r0, src + off_C(D, DV), src + off_m(D, DV), src + off_G(D, DV), src + off_h(D, DV), m + D,
+                    m + D + D * DV, stage);
+}
+
+// total[bh][0 .. F): the sum of a head's converted initial state (slot nseg)
+// and its records 0 .. nseg-1, eight records' loads in flight at a time.
+// grid (ceil(F / 1024), BH).
+__global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, size_t F, float* __restrict__ total,
+                                                 int nseg) {
+  const int bh = blockIdx.y;
+  const size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (p >= F) return;
+  const float* base = rec + (size_t)bh * (nseg + 1) * F + p;
+  float4 x = *reinterpret_cast<const float4*>(base + (size_t)nseg * F);
+  for (int s = 0; s < nseg; s += 8) {
+    float4 u[8];
 #pragma unroll
-    for (int r = 0; r < nS4; ++r) add4(xs[r], reinterpret_cast<const float4*>(x)[tid + 256 * r]);
+    for (int i = 0; i < 8; ++i)
+      u[i] = s + i < nseg ? *reinterpret_cast<const float4*>(base + (size_t)(s + i) * F) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int r = 0; r < nC4; ++r) add4(ys[r], reinterpret_cast<const float4*>(x + off_C(D, DV))[tid + 256 * r]);
-    if (tid < D) {
-      yv += x[off_m(D, DV) + tid];
-      ev += x[off_h(D, DV) + tid];
+    for (int i = 0; i < 8; ++i) {
+      x.x += u[i].x; x.y += u[i].y; x.z += u[i].z; x.w += u[i].w;
     }
   }
-  stage_xy<D, DV>(XT, Y, y, xs, ys, yv);
-#pragma unroll
-  for (int r = 0; r < nS4; ++r) reinterpret_cast<float4*>(out)[tid + 256 * r] = xs[r];
-#pragma unroll
-  for (int r = 0; r < nC4; ++r) reinterpret_cast<float4*>(out + off_C(D, DV))[tid + 256 * r] = ys[r];
-  if (tid < D) {
-    out[off_m(D, DV) + tid] = yv;
-    out[off_h(D, DV) + tid] = ev;      // eta, replaced by h below
-  }
-  // Phi sum into the G slot of the output, then G = S C - Phi in place
-  float* Gout = out + off_G(D, DV);
-  for (int e4 = tid; e4 < D * DV / 4; e4 += 256) {
-    float4 acc = z4;
-    for (int sp = init ? -1 : 0; sp < nsum; ++sp)
-      add4(acc, reinterpret_cast<const float4*>(base + (size_t)(sp < 0 ? nseg : sp) * F + off_G(D, DV))[e4]);
-    reinterpret_cast<float4*>(Gout)[e4] = acc;
-  }
-  __syncthreads();
-  xy_plus<D, DV>(XT, Y, Gout, -1.f, Gout);
-  xv_plus<D>(XT, y, out + off_h(D, DV), -1.f, out + off_h(D, DV));
+  *reinterpret_cast<float4*>(total + (size_t)bh * F + p) = x;
 }
 
 
@@ -1050,12 +1012,6 @@ const Shape* find_shape(int chunk, int d, int dv) {
   return nullptr;
 }
 
-template <int D, int DV>
-hipError_t set_cross_lds(const void* kern, size_t* lds) {
-  *lds = sizeof(float) * ((size_t)D * (D + 4) + (size_t)D * DV + D);
-  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)*lds);
-}
-
 // Launch configuration of one walk kernel (function, threads, LDS bytes).
 struct WalkK {
   const void* fn;
@@ -1214,10 +1170,27 @@ hipError_t run_ws(const Fwd& f, char* ws, hipStream_t s) {
   return hipSuccess;
 }
 
-// DEC: the decayed operator (row-split shapes, no initial or final state).
+template <int D, int DV>
+hipError_t state_to_phi(const float* state, float* segs, int P, int BH, hipStream_t s) {
+  prof_start("init_convert", s);
+  HLA_LAUNCH((k_state_to_phi<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, state, segs, P);
+  prof_stop(s);
+  return hipGetLastError();
+}
+
+template <int D, int DV>
+hipError_t phi_to_state(const float* total, float* state, int BH, hipStream_t s) {
+  prof_start("state", s);
+  HLA_LAUNCH((k_phi_to_state<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, total, state);
+  prof_stop(s);
+  return hipGetLastError();
+}
+
+// state: null, or the decode state that the tokens continue and that receives
+// the state after them, with total a scratch record per head ([BH][F]).
+// DEC: the decayed operator (row-split shapes, no state).
 template <int C, int D, int DV, bool RS, bool DEC = false>
-hipError_t run_shape(const Fwd& f, const float* init, float* final_state, char* ws, int P, int cps,
-                     hipStream_t s) {
+hipError_t run_shape(const Fwd& f, float* state, float* total, char* ws, int P, int cps, hipStream_t s) {
   static_assert(!DEC || RS, "the decayed walk is row-split only");
   const float lg2g = DEC ? (float)std::log2((double)f.gamma) : 0.f;
   const float rho2 = DEC ? (float)std::exp2(2.0 * std::log2((double)f.gamma) * (double)C * (double)cps) : 1.f;
@@ -1229,16 +1202,9 @@ hipError_t run_shape(const Fwd& f, const float* init, float* final_state, char* 
   const uint16_t* v = static_cast<const uint16_t*>(f.v);
   const dim3 grid(P, BH);
   hipError_t e;
-  if (init) {      // slot P <- the initial state in the (S, C, m, Phi, eta) form
-    size_t lds;
-    if ((e = set_cross_lds<D, DV>((const void*)k_init_convert<D, DV>, &lds)) != hipSuccess) return e;
-    prof_start("init_convert", s);
-    HLA_LAUNCH((k_init_convert<D, DV>), dim3(1, BH), dim3(256), lds, s, segs, init, P);
-    prof_stop(s);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+  if (state && (e = state_to_phi<D, DV>(state, segs, P, BH, s)) != hipSuccess) return e;   // slot P
   prof_start("moments", s);
-  if (final_state)
+  if (state)
     HLA_LAUNCH((k_moments<C, D, DV, false, DEC>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 1, lg2g);
   else
     HLA_LAUNCH((k_moments<C, D, DV, false, DEC, false>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 0,
@@ -1250,13 +1216,13 @@ hipError_t run_shape(const Fwd& f, const float* init, float* final_state, char* 
   // row-split walk without an initial state sums up to kWalkSumMax - 1
   // earlier moments itself, which saves this launch.
   float* spre = nullptr;
-  const bool walk_sums = RS && !init && P <= kWalkSumMax;
-  if ((P > 1 || init) && !walk_sums) {
+  const bool walk_sums = RS && !state && P <= kWalkSumMax;
+  if ((P > 1 || state) && !walk_sums) {
     spre = reinterpret_cast<float*>(ws + legacy_spre_offset(BH, f.n, P, C, D, DV));
     const float rhoS = DEC ? (float)std::exp2((double)lg2g * (double)C * (double)cps) : 1.f;
     prof_start("seg_prefix", s);
     HLA_LAUNCH(k_seg_prefix, dim3((D * D + 1023) / 1024, BH), dim3(256), 0, s, segs, state_floats(D, DV), 0, D * D,
-               init ? 1 : 0, spre, P, rhoS);
+               state ? 1 : 0, spre, P, rhoS);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1267,18 +1233,18 @@ hipError_t run_shape(const Fwd& f, const float* init, float* final_state, char* 
                           cps, P, 0, 0.f, lg2g);
   prof_stop(s);
   if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
-  if (final_state) {
-    size_t lds;
-    if ((e = set_cross_lds<D, DV>((const void*)k_total<D, DV>, &lds)) != hipSuccess) return e;
+  if (state) {
+    const size_t F = state_floats(D, DV);
     prof_start("total", s);
-    HLA_LAUNCH((k_total<D, DV>), dim3(BH), dim3(256), lds, s, segs, init, final_state, P, P);
+    HLA_LAUNCH(k_rec_sum, dim3((F + 1023) / 1024, BH), dim3(256), 0, s, segs, F, total, P);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = phi_to_state<D, DV>(total, state, BH, s)) != hipSuccess) return e;
   }
-  if (f.out && (P > 1 || init || f.normalized)) {
+  if (f.out && (P > 1 || state || f.normalized)) {
     float* carry = den + (((size_t)BH * f.n + (size_t)BH * ((f.n + C - 1) / C) * D + 63) & ~size_t(63));
     prof_start("carry", s);
-    HLA_LAUNCH((k_carry<D, DV>), dim3((D * DV / 8 + D + 255) / 256, BH), dim3(256), 0, s, segs, init, carry, P,
+    HLA_LAUNCH((k_carry<D, DV>), dim3((D * DV / 8 + D + 255) / 256, BH), dim3(256), 0, s, segs, state ? 1 : 0, carry, P,
                rho2);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1290,7 +1256,7 @@ hipError_t run_shape(const Fwd& f, const float* init, float* final_state, char* 
     const int M = (f.n + C - 1) / C, tpw = fix_tpw(M, BH);
     prof_start("fix", s);
     HLA_LAUNCH((k_fix<C, D, DV, DEC>), dim3((M + tpw - 1) / tpw, BH), dim3(FC::NT), FC::lds, s, q, f.out, den,
-               carry, f.normalized ? f.den_out : nullptr, init ? 1 : 0, f.n, cps, P, f.normalized, f.eps, tpw,
+               carry, f.normalized ? f.den_out : nullptr, state ? 1 : 0, f.n, cps, P, f.normalized, f.eps, tpw,
                lg2g);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1364,24 +1330,24 @@ size_t fused_workspace_bytes(int BH, int n, int d, int dv, int chunk) {
   return legacy;
 }
 
-hipError_t launch_fused(const Fwd& f, const float* init, float* final_state, void* workspace, hipStream_t s) {
+hipError_t launch_fused(const Fwd& f, float* state, float* total, void* workspace, hipStream_t s) {
   const Shape* sh = find_shape(f.chunk, f.d, f.dv);
   if (!sh) return hipErrorNotSupported;
   int P, cps;
   fused_plan(*sh, f.BH, f.n, &P, &cps);
   char* ws = static_cast<char*>(workspace);
-  if (f.gamma == 1.f && !init && !final_state && ws_shape(*sh) && !legacy_pipeline()) return run_ws(f, ws, s);
+  if (f.gamma == 1.f && !state && ws_shape(*sh) && !legacy_pipeline()) return run_ws(f, ws, s);
   if (f.gamma != 1.f) {           // decayed: row-split shapes only, no states
-    if (!row_split_shape(*sh) || init || final_state) return hipErrorNotSupported;
-    if (sh->D == 64) return run_shape<64, 64, 64, true, true>(f, init, final_state, ws, P, cps, s);
-    return run_shape<64, 128, 128, true, true>(f, init, final_state, ws, P, cps, s);
+    if (!row_split_shape(*sh) || state) return hipErrorNotSupported;
+    if (sh->D == 64) return run_shape<64, 64, 64, true, true>(f, state, total, ws, P, cps, s);
+    return run_shape<64, 128, 128, true, true>(f, state, total, ws, P, cps, s);
   }
   if (row_split_shape(*sh)) {
-    if (sh->D == 64) return run_shape<64, 64, 64, true>(f, init, final_state, ws, P, cps, s);
-    return run_shape<64, 128, 128, true>(f, init, final_state, ws, P, cps, s);
+    if (sh->D == 64) return run_shape<64, 64, 64, true>(f, state, total, ws, P, cps, s);
+    return run_shape<64, 128, 128, true>(f, state, total, ws, P, cps, s);
   }
 #define HLA_SHAPE(C_, D_, DV_) \
-  if (sh->C == C_ && sh->D == D_ && sh->DV == DV_) return run_shape<C_, D_, DV_, false>(f, init, final_state, ws, P, cps, s);
+  if (sh->C == C_ && sh->D == D_ && sh->DV == DV_) return run_shape<C_, D_, DV_, false>(f, state, total, ws, P, cps, s);
   HLA_SHAPE(64, 64, 64)
   HLA_SHAPE(32, 32, 32)
   HLA_SHAPE(64, 32, 32)

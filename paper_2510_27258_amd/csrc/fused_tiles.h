@@ -451,10 +451,11 @@ __global__ __launch_bounds__(256) void k_seg_prefix(const float* __restrict__ re
 // Phi_c[16s + 8(lane/32) + j][32ct + lane%32], j = 0..7: D*DV/8 pieces of
 // 16 bytes, all hi pieces then all lo pieces), then eta_c in fp32 [D].
 // grid (ceil((D*DV/8 + D) / 256), BH); reads and writes coalesced.
+// init: whether slot nseg holds an initial state.
 // rho2: attenuation of a carry over one segment (gamma^(2L) with decay, else 1):
 // carry_{s+1} = rho2 carry_s + bracket_s.
 template <int D, int DV>
-__global__ __launch_bounds__(256) void k_carry(const float* __restrict__ rec, const float* __restrict__ init,
+__global__ __launch_bounds__(256) void k_carry(const float* __restrict__ rec, int init,
                                                float* __restrict__ carry, int nseg, float rho2) {
   constexpr int NC = D * DV + D, NP = D * DV / 8, KD = D / 16;
   const int bh = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;

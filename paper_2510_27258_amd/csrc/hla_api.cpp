@@ -449,15 +449,16 @@ int hla2_prefill(hla2_state* st, const void* q, const void* k, const void* v, in
   char* tail = base + (cws > fws ? cws : fws);
   float* total = reinterpret_cast<float*>(tail);
   float* init = reinterpret_cast<float*>(tail + align256(sizeof(float) * (size_t)BH * hla::state_floats(d, dv)));
-  // the state's packed records to full ones, the forward from them, the new
-  // total packed back into the state
-  hipError_t e = hla::launch_state_unpack(state, init, BH, d, dv, s);
-  if (e != hipSuccess) return hip_fail(e, "state unpack");
+  hipError_t e;
   if (hla::fused_supported(n, d, dv, chunk, dtype, out ? masked : 1)) {
     hla::Fwd f{q, k, v, out, BH, n, d, dv, chunk, masked, normalized, dtype, eps};
-    e = hla::launch_fused(f, init, total, workspace, s);
+    e = hla::launch_fused(f, state, total, workspace, s);
     if (e != hipSuccess) return hip_fail(e, "fused prefill");
   } else {
+    // the state's packed records to full ones, the forward from them, the new
+    // total packed back into the state
+    e = hla::launch_state_unpack(state, init, BH, d, dv, s);
+    if (e != hipSuccess) return hip_fail(e, "state unpack");
     const int cc = path_chunk(chunk), Mc = (n + cc - 1) / cc;
     e = hla::launch_chunk_summaries(q, k, v, states, BH, n, d, dv, cc, dtype, s);
     if (e != hipSuccess) return hip_fail(e, "chunk summaries");
@@ -468,9 +469,9 @@ int hla2_prefill(hla2_state* st, const void* q, const void* k, const void* v, in
       e = hla::launch_readout(f, prefix, s);
       if (e != hipSuccess) return hip_fail(e, "readout");
     }
+    e = hla::launch_state_pack(total, state, BH, d, dv, s);
+    if (e != hipSuccess) return hip_fail(e, "state pack");
   }
-  e = hla::launch_state_pack(total, state, BH, d, dv, s);
-  if (e != hipSuccess) return hip_fail(e, "state pack");
   return ok();
 }
 
