@@ -427,7 +427,7 @@ hipError_t run_ahla(const Fwd& f, char* ws, int P, int cps, hipStream_t s) {
   hipError_t e;
   if (P > 1) {
     prof_start("ahla_moments", s);
-    HLA_LAUNCH((k_moments<C, D, D, true>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 1, 0.f);
+    HLA_LAUNCH((k_moments<C, D, D, true>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 1, 0.f, MomRange{cps, cps, 1});
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (P > kAhlaWalkSumMax) {

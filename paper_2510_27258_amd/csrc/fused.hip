@@ -17,7 +17,7 @@
 // With a decode state, k_state_to_phi converts it to the (S, C, m, Phi, eta)
 // form first; k_rec_sum sums all records and k_phi_to_state converts the sum
 // back into the state.  k_moments, k_carry and k_fix live in fused_tiles.h.
-// At d = dv = 128 without states the forward takes the two-pass plan of
+// At d = dv = 128 (with outputs wanted) the forward takes the two-pass plan of
 // fused_ws.h instead (run_ws): segment 0's output walk beside the summary
 // walks of the later segments, the brackets, then the other segments' output
 // walks from their true carries, so that every output row is written once.
@@ -174,13 +174,17 @@ __global__ __launch_bounds__(4 * DV) void k_state_to_phi(const float* __restrict
   cross_rows<D, DV>(Sr, r0, C, m, m + D, m + D + D * DV, dst + off_G(D, DV), dst + off_h(D, DV), stage);
 }
 
-// total: [BH][F] records in the (S, C, m, Phi, eta) form.
+// C and m from the [BH][F] records total, S, Phi and eta from the records
+// last (stride floats a head).
 template <int D, int DV>
-__global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict__ total, float* __restrict__ state) {
+__global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict__ total,
+                                                         const float* __restrict__ last, size_t stride,
+                                                         float* __restrict__ state) {
   constexpr int ld = D + 17, NT = 4 * DV;
   __shared__ float Sr[16 * ld];
   const int r0 = blockIdx.x * 16, bh = blockIdx.y, tid = threadIdx.x;
   const float* src = total + (size_t)bh * state_floats(D, DV);
+  const float* end = last + (size_t)bh * stride;
   float* dst = state + (size_t)bh * dstate_floats(D, DV);
   float* C = dst + packed_s_floats(D);
   float* m = C + D * DV;
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict
 #pragma unroll
     for (int i = 0; i < 16 * D / NT; ++i) {
       const int e = tid + NT * i, r = r0 + e / D, j = e % D;
-      const float x = src[(size_t)r * D + j];
+      const float x = end[(size_t)r * D + j];
       Sr[(e / D) * ld + j] = x;
       if (j >= r) dst[r < D / 2 ? r * (D + 1) + j - r : (D - 1 - r) * (D + 1) + j + 1] = x;
     }
@@ -199,18 +203,19 @@ __global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict
     }
     if (tid < 16) m[r0 + tid] = src[off_m(D, DV) + r0 + tid];
   };
-  cross_rows<D, DV>(Sr, r0, src + off_C(D, DV), src + off_m(D, DV), src + off_G(D, DV), src + off_h(D, DV), m + D,
+  cross_rows<D, DV>(Sr, r0, src + off_C(D, DV), src + off_m(D, DV), end + off_G(D, DV), end + off_h(D, DV), m + D,
                     m + D + D * DV, stage);
 }
 
-// total[bh][0 .. F): the sum of a head's converted initial state (slot nseg)
-// and its records 0 .. nseg-1, eight records' loads in flight at a time.
-// grid (ceil(F / 1024), BH).
-__global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, size_t F, float* __restrict__ total,
-                                                 int nseg) {
+// total[bh][off .. off + len): the sum of a head's converted initial state
+// (slot nseg) and its records 0 .. nseg-1, eight records' loads in flight at a
+// time.  grid (ceil(len / 1024), BH).
+__global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, size_t F, int off, int len,
+                                                 float* __restrict__ total, int nseg) {
   const int bh = blockIdx.y;
-  const size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (p >= F) return;
+  size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (p >= (size_t)len) return;
+  p += off;
   const float* base = rec + (size_t)bh * (nseg + 1) * F + p;
   float4 x = *reinterpret_cast<const float4*>(base + (size_t)nseg * F);
   for (int s = 0; s < nseg; s += 8) {
@@ -1055,8 +1060,7 @@ size_t legacy_ws_bytes(int BH, int n, int P, int C, int d, int dv) {
   return legacy_spre_offset(BH, n, P, C, d, dv) + sizeof(float) * (size_t)BH * P * d * d + 256;
 }
 
-// Workspace of the two-pass pipeline (d = dv = 128, no initial or final
-// state): records [BH][P + 1][F] | S prefixes [BH][P][d d] | Phi, eta carries
+// Workspace of the two-pass pipeline (d = dv = 128): records [BH][P + 1][F] | S prefixes [BH][P][d d] | Phi, eta carries
 // [BH][P][d dv + d].
 size_t ws_pipeline_bytes(int BH, int P) {
   constexpr int D = CfgWS::D, DV = CfgWS::DV;
@@ -1115,8 +1119,32 @@ hipError_t launch_ws(const void* fn, dim3 grid, hipStream_t s, void** args) {
   return prof_launch(fn, grid, dim3(CfgWS::NT), args, CfgWS::bytes, s);
 }
 
-// The forward at d = dv = 128 (64-token tiles) without states, every output
-// row written once (plan in ws_plan):
+template <int D, int DV>
+hipError_t state_to_phi(const float* state, float* segs, int P, int BH, hipStream_t s) {
+  prof_start("init_convert", s);
+  HLA_LAUNCH((k_state_to_phi<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, state, segs, P);
+  prof_stop(s);
+  return hipGetLastError();
+}
+
+// Part [off, off + len) of every head's records and initial state, summed into total.
+hipError_t rec_sum(const float* segs, size_t F, int off, int len, float* total, int P, int BH, hipStream_t s) {
+  prof_start("total", s);
+  HLA_LAUNCH(k_rec_sum, dim3((len + 1023) / 1024, BH), dim3(256), 0, s, segs, F, off, len, total, P);
+  prof_stop(s);
+  return hipGetLastError();
+}
+
+template <int D, int DV>
+hipError_t phi_to_state(const float* total, const float* last, size_t stride, float* state, int BH, hipStream_t s) {
+  prof_start("state", s);
+  HLA_LAUNCH((k_phi_to_state<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, total, last, stride, state);
+  prof_stop(s);
+  return hipGetLastError();
+}
+
+// The forward at d = dv = 128 (64-token tiles), every output row written once
+// (plan in ws_plan):
 //   1. k_walk_ws_first: segment 0's output walk, and the summary walks of
 //      segments 1 .. P-2 from a zero state (S, C, m, Phi, eta records);
 //   2. k_ws_bracket: the S prefixes, summed from the records, and each
@@ -1124,7 +1152,14 @@ hipError_t launch_ws(const void* fn, dim3 grid, hipStream_t s, void** args) {
 //      k_seg_prefix: the running sums of the brackets, the Phi, eta carries;
 //   3. k_walk_ws_out over segments 1 .. P-1 from their true carries.
 // With P = 1, step 3 alone over whole heads.
-hipError_t run_ws(const Fwd& f, char* ws, hipStream_t s) {
+// With a decode state (total: a scratch record per head) segment 0 starts from
+// it instead of from zero, so record 0 holds it and steps 2 and 3 are the
+// same.  The last output walk leaves S, Phi and eta after the last token in
+// record P - 1; only C and m need a sum, for which the segments without a
+// summary walk (the first and the last) get theirs from a moments launch.
+// Against the walk + k_fix pipeline, two prefills of 4096 and 3904 tokens on
+// 32 heads: 367 -> 307 us.
+hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_t s) {
   constexpr int D = CfgWS::D, DV = CfgWS::DV;
   const int BH = f.BH;
   int P, cps, c0;
@@ -1140,10 +1175,21 @@ hipError_t run_ws(const Fwd& f, char* ws, hipStream_t s) {
   float* den = f.normalized ? f.den_out : nullptr;
   int n = f.n, normalized = f.normalized;
   float eps = f.eps;
+  int cont = state ? 1 : 0;
   hipError_t e;
+  if (state) {
+    if ((e = state_to_phi<D, DV>(state, segs, P, BH, s)) != hipSuccess) return e;   // slot P
+    // C = Q^T V and m = Q^T 1 of segments 0 and P - 1 (the K^T V form, with q for k)
+    const int last = P > 1 ? c0 + (P - 2) * cps : 0;
+    prof_start("moments", s);
+    HLA_LAUNCH((k_moments<CfgWS::C, D, DV, true>), dim3(P > 1 ? 2 : 1, BH), dim3(kThreads), 0, s, q, q, v, segs, n,
+               cps, P, 1, 0.f, MomRange{last, c0, P - 1});
+    prof_stop(s);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   if (P > 1) {
     prof_start("walk_first", s);
-    void* a1[] = {&q, &k, &v, &out, &den, &segs, &n, &c0, &cps, &P, &normalized, &eps};
+    void* a1[] = {&q, &k, &v, &out, &den, &segs, &n, &c0, &cps, &P, &cont, &normalized, &eps};
     e = launch_ws((const void*)k_walk_ws_first, dim3(P - 1, BH), s, a1);
     prof_stop(s);
     if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
@@ -1163,27 +1209,16 @@ hipError_t run_ws(const Fwd& f, char* ws, hipStream_t s) {
   const float* cp = P > 1 ? carry : nullptr;
   int seg0 = P > 1 ? 1 : 0;
   prof_start("walk", s);
-  void* a2[] = {&q, &k, &v, &out, &den, &sp, &cp, &n, &c0, &cps, &P, &seg0, &normalized, &eps};
+  float* fin = state ? segs : nullptr;
+  void* a2[] = {&q, &k, &v, &out, &den, &sp, &cp, &fin, &n, &c0, &cps, &P, &seg0, &normalized, &eps};
   e = launch_ws((const void*)k_walk_ws_out, dim3(P > 1 ? P - 1 : 1, BH), s, a2);
   prof_stop(s);
   if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
+  if (state) {
+    if ((e = rec_sum(segs, F, (int)off_C(D, DV), D * DV + D, total, P, BH, s)) != hipSuccess) return e;
+    return phi_to_state<D, DV>(total, segs + (size_t)(P - 1) * F, (P + 1) * F, state, BH, s);
+  }
   return hipSuccess;
-}
-
-template <int D, int DV>
-hipError_t state_to_phi(const float* state, float* segs, int P, int BH, hipStream_t s) {
-  prof_start("init_convert", s);
-  HLA_LAUNCH((k_state_to_phi<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, state, segs, P);
-  prof_stop(s);
-  return hipGetLastError();
-}
-
-template <int D, int DV>
-hipError_t phi_to_state(const float* total, float* state, int BH, hipStream_t s) {
-  prof_start("state", s);
-  HLA_LAUNCH((k_phi_to_state<D, DV>), dim3(D / 16, BH), dim3(4 * DV), 0, s, total, state);
-  prof_stop(s);
-  return hipGetLastError();
 }
 
 // state: null, or the decode state that the tokens continue and that receives
@@ -1205,10 +1240,11 @@ hipError_t run_shape(const Fwd& f, float* state, float* total, char* ws, int P, 
   if (state && (e = state_to_phi<D, DV>(state, segs, P, BH, s)) != hipSuccess) return e;   // slot P
   prof_start("moments", s);
   if (state)
-    HLA_LAUNCH((k_moments<C, D, DV, false, DEC>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 1, lg2g);
+    HLA_LAUNCH((k_moments<C, D, DV, false, DEC>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 1, lg2g,
+               MomRange{cps, cps, 1});
   else
     HLA_LAUNCH((k_moments<C, D, DV, false, DEC, false>), grid, dim3(kThreads), 0, s, q, k, v, segs, f.n, cps, P, 0,
-               lg2g);
+               lg2g, MomRange{cps, cps, 1});
   prof_stop(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // S prefix of every segment (the walks each read one): init + the earlier
@@ -1235,11 +1271,8 @@ hipError_t run_shape(const Fwd& f, float* state, float* total, char* ws, int P, 
   if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
   if (state) {
     const size_t F = state_floats(D, DV);
-    prof_start("total", s);
-    HLA_LAUNCH(k_rec_sum, dim3((F + 1023) / 1024, BH), dim3(256), 0, s, segs, F, total, P);
-    prof_stop(s);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = phi_to_state<D, DV>(total, state, BH, s)) != hipSuccess) return e;
+    if ((e = rec_sum(segs, F, 0, (int)F, total, P, BH, s)) != hipSuccess) return e;
+    if ((e = phi_to_state<D, DV>(total, total, F, state, BH, s)) != hipSuccess) return e;
   }
   if (f.out && (P > 1 || state || f.normalized)) {
     float* carry = den + (((size_t)BH * f.n + (size_t)BH * ((f.n + C - 1) / C) * D + 63) & ~size_t(63));
@@ -1336,7 +1369,7 @@ hipError_t launch_fused(const Fwd& f, float* state, float* total, void* workspac
   int P, cps;
   fused_plan(*sh, f.BH, f.n, &P, &cps);
   char* ws = static_cast<char*>(workspace);
-  if (f.gamma == 1.f && !state && ws_shape(*sh) && !legacy_pipeline()) return run_ws(f, ws, s);
+  if (f.gamma == 1.f && f.out && ws_shape(*sh) && !legacy_pipeline()) return run_ws(f, state, total, ws, s);
   if (f.gamma != 1.f) {           // decayed: row-split shapes only, no states
     if (!row_split_shape(*sh) || state) return hipErrorNotSupported;
     if (sh->D == 64) return run_shape<64, 64, 64, true, true>(f, state, total, ws, P, cps, s);

@@ -41,6 +41,14 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){x0 - h0, x1 - h1}, b2));
 }
 
+// A pair in three pieces, x = hi + mid + lo up to 2^-24 of x.
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){x0, x1}, b2));
+  split2(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xffff0000u), mid, lo);
+}
+
 // Buffer resource over [p, p + bytes): loads past the end return zero and
 // stores past the end are dropped, which zero-fills the ragged last chunk and
 // clips its outputs.  Offsets are 32-bit bytes from p.
@@ -212,12 +220,18 @@ __device__ __forceinline__ void store_N(const f32x16& acc, uint16_t* Xh, uint16_
 // DEC (decay gamma = 2^lg2g; S only): S = sum_t gamma^(e - t) k_t k_t^T with e
 // the segment's last token, the weight applied to one factor per token in
 // fp32 and split hi/lo.
+// Grid column x covers the tiles from x * mr.stride on, mr.len0 of them for
+// x = 0 and cps for the others, and writes slot x * mr.slot: {cps, cps, 1} for
+// every segment in turn.
 // CM = false compiles the S-only form alone (want_cm is ignored): without the
 // C and m registers and buffers it runs at a higher occupancy.
+struct MomRange {
+  int stride, len0, slot;
+};
 template <int C, int D, int DV, bool KV = false, bool DEC = false, bool CM = true>
 __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ v, float* __restrict__ rec, int n,
-                                                      int cps, int nseg, int want_cm, float lg2g) {
+                                                      int cps, int nseg, int want_cm, float lg2g, MomRange mr) {
   constexpr int DT = D / 32, VT = DV / 32, KC = C / 16;
   constexpr int nS = (DT * DT + kWaves - 1) / kWaves, nC = (DT * VT + kWaves - 1) / kWaves;
   constexpr int segQ = C * D / 8, segV = C * DV / 8;
@@ -231,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
   if (!CM) want_cm = 0;
   const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, l = tid & 63, lr = l & 31, lg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int M = (n + C - 1) / C, c0 = seg * cps, c1 = min(M, c0 + cps);
+  const int M = (n + C - 1) / C, c0 = seg * mr.stride, c1 = min(M, c0 + (seg == 0 ? mr.len0 : cps));
   const rsrc_t rq = make_rsrc(q + (size_t)bh * n * D, (uint32_t)n * D * 2);
   const rsrc_t rk = make_rsrc(k + (size_t)bh * n * D, (uint32_t)n * D * 2);
   const rsrc_t rv = make_rsrc(v + (size_t)bh * n * DV, (uint32_t)n * DV * 2);
@@ -396,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
       for (int ww = 0; ww < kWaves; ++ww) macc += part[ww * D + tid];
     }
   }
-  float* r = rec + ((size_t)bh * (nseg + 1) + seg) * state_floats(D, DV);
+  float* r = rec + ((size_t)bh * (nseg + 1) + seg * mr.slot) * state_floats(D, DV);
 #pragma unroll
   for (int i = 0; i < nS; ++i) {
     const int ti = w + kWaves * i;

@@ -21,9 +21,9 @@
 // computed operand is split into bf16 hi + lo, q/k/v are exact, fp32
 // accumulation.
 //
-// Two-pass plan (no initial or final state).  Segment 0 holds c0 tiles and
+// Two-pass plan.  Segment 0 holds c0 tiles and
 // every later segment cps tiles (the last the rest); the first launch runs,
-// side by side, the output walk of segment 0 (its carry is zero) and the
+// side by side, the output walk of segment 0 (its carry is known) and the
 // summary walks of segments 1 .. P-2 from a zero state, the latter also
 // forming C = Q^T V and m = Q^T 1 of their tiles; the S prefixes, the
 // brackets (Eq. semidirect in the Phi form: the bracket of segment s is
@@ -469,31 +469,39 @@ __device__ __forceinline__ void walk_ws(uint16_t* lds,
 }
 
 // First launch of the two-pass plan, grid (P - 1, BH): segment 0's output
-// walk (zero carry) and the summary walks of segments 1 .. P-2 (zero state),
-// each writing its record rec[bh][seg].
+// walk (from the initial state in slot nseg with cont, else from zero) and the
+// summary walks of segments 1 .. P-2 (zero state), each writing its record
+// rec[bh][seg].
 __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_first(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ out, float* __restrict__ den_out, float* __restrict__ rec, int n, int c0, int cps,
-    int nseg, int normalized, float eps) {
+    int nseg, int cont, int normalized, float eps) {
   extern __shared__ __align__(16) uint16_t lds[];
+  constexpr int D = CfgWS::D, DV = CfgWS::DV;
   int seg, bh;
   seg_head(seg, bh);
   int cb, nt;
   ws_range(seg, c0, cps, (n + CfgWS::C - 1) / CfgWS::C, cb, nt);
-  float* r = rec + ((size_t)bh * (nseg + 1) + seg) * state_floats(CfgWS::D, CfgWS::DV);
+  float* r = rec + ((size_t)bh * (nseg + 1) + seg) * state_floats(D, DV);
+  const float* init = cont ? rec + ((size_t)bh * (nseg + 1) + nseg) * state_floats(D, DV) : nullptr;
   if (seg == 0)
-    walk_ws<false>(lds, q, k, v, out, den_out, nullptr, nullptr, r, bh, n, cb, nt, normalized, eps);
+    walk_ws<false>(lds, q, k, v, out, den_out, init, init ? init + off_G(D, DV) : nullptr, r, bh, n, cb, nt,
+                   normalized, eps);
   else
     walk_ws<true>(lds, q, k, v, nullptr, nullptr, nullptr, nullptr, r, bh, n, cb, nt, 0, 0.f);
 }
 
 // Output walks from the true carries, grid (walks, BH): grid column x walks
 // segment seg0 + x.  spre: [BH][nseg][D*D] S prefixes and carry:
-// [BH][nseg][D*DV + D] Phi, eta carries (both null for a single segment: zero).
+// [BH][nseg][D*DV + D] Phi, eta carries (both null for a single segment).
+// fin: null, or the records: a single segment then starts from the initial
+// state in slot nseg, and the last segment's walk writes its ending S, Phi
+// and eta into record nseg - 1.
 __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_out(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ out, float* __restrict__ den_out, const float* __restrict__ spre,
-    const float* __restrict__ carry, int n, int c0, int cps, int nseg, int seg0, int normalized, float eps) {
+    const float* __restrict__ carry, float* __restrict__ fin, int n, int c0, int cps, int nseg, int seg0,
+    int normalized, float eps) {
   constexpr int D = CfgWS::D, DV = CfgWS::DV;
   extern __shared__ __align__(16) uint16_t lds[];
   int seg, bh;
@@ -503,7 +511,15 @@ __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_out(
   ws_range(seg, c0, cps, (n + CfgWS::C - 1) / CfgWS::C, cb, nt);
   const float* si = spre ? spre + ((size_t)bh * nseg + seg) * D * D : nullptr;
   const float* ci = carry ? carry + ((size_t)bh * nseg + seg) * (D * DV + D) : nullptr;
-  walk_ws<false>(lds, q, k, v, out, den_out, si, ci, nullptr, bh, n, cb, nt, normalized, eps);
+  float* r = nullptr;
+  if (fin && seg == nseg - 1) {
+    r = fin + ((size_t)bh * (nseg + 1) + seg) * state_floats(D, DV);
+    if (!spre) {                     // one segment: slot 1 holds the initial state
+      si = r + state_floats(D, DV);
+      ci = si + off_G(D, DV);
+    }
+  }
+  walk_ws<false>(lds, q, k, v, out, den_out, si, ci, r, bh, n, cb, nt, normalized, eps);
 }
 
 // The S prefixes and the brackets of the two-pass plan (Eq. semidirect in
@@ -514,16 +530,20 @@ __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_out(
 // from a zero start, also b_s = (Phi_s + S_{<s} C_s, eta_s + S_{<s} m_s),
 // written in place of (Phi_s, eta_s); record 0 already holds b_0.
 // grid (nseg - 1, BH), 1024 threads, one workgroup per (segment, head), a
-// head's workgroups on one XCD.  S_{<s} and C_s are split into bf16 hi + lo
-// in LDS, as every computed operand of the walks, and wave w forms the
-// 32 x 32 tile (w / 4, w % 4) of S_{<s} C_s in three passes (hi hi, hi lo,
-// lo hi) with fp32 accumulation.
+// head's workgroups on one XCD.  S_{<s} and C_s are split into three bf16
+// pieces (24 bits: the fp32 values) in LDS, one half of the contraction at a
+// time, and wave w forms the 32 x 32 tile (w / 4, w % 4) of S_{<s} C_s from
+// the six products of at least 2^-16 with fp32 accumulation: the bracket is
+// what the later segments' carries are summed from, and with two pieces
+// (three products) it was the larger part of their error (prefill of 8000
+// tokens on 32 heads, outputs 4.3-4.7e-6 from the 64-bit result, now 2.9e-6).  The
+// loads bound it: 1 MB a workgroup at 8 segments.
 template <int D, int DV>
 __global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, float* __restrict__ spre, int nseg) {
-  constexpr int ldS = D + kPad, ldC = DV + 16, NT = 1024;   // ldC: C is read through the transpose unit
+  constexpr int KH = D / 2, ldS = KH + kPad, ldC = DV + 16, NT = 1024;   // ldC: C is read through the transpose unit
   static_assert(D == 128 && DV == 128, "16 waves of 32 x 32 output tiles");
-  __shared__ __align__(16) uint16_t Sh[D * ldS], Sl[D * ldS], Ch[D * ldC], Cl[D * ldC];
-  __shared__ float mv[D], ep[8 * D];
+  __shared__ __align__(16) uint16_t Sp[3][D * ldS], Cp[3][KH * ldC];
+  __shared__ float mv[D], ep[D];
   int s, bh;
   seg_head(s, bh);
   s += 1;
@@ -532,6 +552,21 @@ __global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, fl
   const size_t F = state_floats(D, DV);
   float* r = rec + ((size_t)bh * (nseg + 1) + s) * F;
   constexpr int NS4 = D * D / 4 / NT;
+  // C_s and Phi_s first (the last segment's record is not read: it has no bracket)
+  const bool own = s < nseg - 1;
+  float4 cx[NS4];
+  f32x16 acc;        // b_s: element e is row r0 + acc_row(e, lg), column c0 + lr
+  float eta = 0.f, m = 0.f;
+  if (own) {
+#pragma unroll
+    for (int i = 0; i < NS4; ++i) cx[i] = reinterpret_cast<const float4*>(r + off_C(D, DV))[tid + NT * i];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = r[off_G(D, DV) + (size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr];
+    if (tid < D) {
+      eta = r[off_h(D, DV) + tid];
+      m = r[off_m(D, DV) + tid];
+    }
+  }
   // S_{<s}: the earlier records' S slots, two records' loads in flight at a time
   float4 sx[NS4];
 #pragma unroll
@@ -555,55 +590,60 @@ __global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, fl
   float4* spw = reinterpret_cast<float4*>(spre + ((size_t)bh * nseg + s) * D * D);
 #pragma unroll
   for (int i = 0; i < NS4; ++i) spw[tid + NT * i] = sx[i];
-  if (s == nseg - 1) return;   // the last segment has no summary, so no bracket
+  if (!own) return;
+  if (tid < D) mv[tid] = m;
+  auto put = [](uint16_t* p0, uint16_t* p1, uint16_t* p2, const float4& x) {
+    uint32_t h0, h1, m0, m1, l0, l1;
+    split3(x.x, x.y, h0, m0, l0);
+    split3(x.z, x.w, h1, m1, l1);
+    *reinterpret_cast<uint2*>(p0) = make_uint2(h0, h1);
+    *reinterpret_cast<uint2*>(p1) = make_uint2(m0, m1);
+    *reinterpret_cast<uint2*>(p2) = make_uint2(l0, l1);
+  };
+  const int row = tid / (D / 4), col = 4 * (tid % (D / 4));   // of piece 0; piece i is 32 rows further down
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NS4; ++i)
+      if (col / KH == h) {
+        const int o = (row + 32 * i) * ldS + col - KH * h;
+        put(Sp[0] + o, Sp[1] + o, Sp[2] + o, sx[i]);
+      }
+#pragma unroll
+    for (int i = 0; i < NS4 / 2; ++i) {
+      const int o = (row + 32 * i) * ldC + col;
+      put(Cp[0] + o, Cp[1] + o, Cp[2] + o, cx[i + NS4 / 2 * h]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < KH / 16; ++ks) {
+      bf16x8 a[3], b[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        a[j] = frag(Sp[j], ldS, r0, 16 * ks);
+        b[j] = frag_tr(Cp[j], ldC, c0, 16 * ks);
+      }
+      acc = mfma(a[0], b[0], acc);
+      acc = mfma(a[0], b[1], acc);
+      acc = mfma(a[1], b[0], acc);
+      acc = mfma(a[0], b[2], acc);
+      acc = mfma(a[1], b[1], acc);
+      acc = mfma(a[2], b[0], acc);
+    }
+  }
+  // S_{<s} m_s from the registers: 32 lanes hold a row
 #pragma unroll
   for (int i = 0; i < NS4; ++i) {
-    const int e = tid + NT * i, row = e / (D / 4), c4 = e % (D / 4);
-    const float4 x = sx[i];
-    const float4 y = *reinterpret_cast<const float4*>(r + off_C(D, DV) + (size_t)row * DV + 4 * c4);
-    uint32_t h0, h1, l0, l1;
-    split2(x.x, x.y, h0, l0);
-    split2(x.z, x.w, h1, l1);
-    *reinterpret_cast<uint2*>(Sh + row * ldS + 4 * c4) = make_uint2(h0, h1);
-    *reinterpret_cast<uint2*>(Sl + row * ldS + 4 * c4) = make_uint2(l0, l1);
-    split2(y.x, y.y, h0, l0);
-    split2(y.z, y.w, h1, l1);
-    *reinterpret_cast<uint2*>(Ch + row * ldC + 4 * c4) = make_uint2(h0, h1);
-    *reinterpret_cast<uint2*>(Cl + row * ldC + 4 * c4) = make_uint2(l0, l1);
-  }
-  if (tid < D) mv[tid] = r[off_m(D, DV) + tid];
-  f32x16 acc;        // b_s: element e is row r0 + acc_row(e, lg), column c0 + lr
+    float x = sx[i].x * mv[col] + sx[i].y * mv[col + 1] + sx[i].z * mv[col + 2] + sx[i].w * mv[col + 3];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = r[off_G(D, DV) + (size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr];
-  const float eta = tid < D ? r[off_h(D, DV) + tid] : 0.f;
-  __syncthreads();
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-    const bf16x8 ah = frag(Sh, ldS, r0, 16 * ks), al = frag(Sl, ldS, r0, 16 * ks);
-    const bf16x8 bh_ = frag_tr(Ch, ldC, c0, 16 * ks), bl_ = frag_tr(Cl, ldC, c0, 16 * ks);
-    acc = mfma(ah, bh_, acc);
-    acc = mfma(ah, bl_, acc);
-    acc = mfma(al, bh_, acc);
-  }
-  {  // S_{<s} m_s: eight partial sums of 16 k per row, then their total
-    const int row = tid % D, part = tid / D;
-    float x = 0.f;
-#pragma unroll
-    for (int j = 0; j < D / 8; ++j) {
-      const int kk = part * (D / 8) + j;
-      x += (bf16_to_f(Sh[row * ldS + kk]) + bf16_to_f(Sl[row * ldS + kk])) * mv[kk];
-    }
-    ep[part * D + row] = x;
+    for (int o = 1; o < 32; o <<= 1) x += __shfl_xor(x, o);
+    if (col == 0) ep[row + 32 * i] = x;
   }
 #pragma unroll
   for (int e = 0; e < 16; ++e) r[off_G(D, DV) + (size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr] = acc[e];
   __syncthreads();
-  if (tid < D) {
-    float e = eta;
-#pragma unroll
-    for (int p = 0; p < 8; ++p) e += ep[p * D + tid];
-    r[off_h(D, DV) + tid] = e;
-  }
+  if (tid < D) r[off_h(D, DV) + tid] = eta + ep[tid];
 }
 
 }  // namespace
