@@ -217,6 +217,11 @@ __device__ __forceinline__ void la_pass(
 
   for (int it = 0; it < nt; ++it) {
     const int c = tile_of(it);
+    // the lane index, at d = 128 made opaque once per tile: the fragments'
+    // lane offsets are formed once per tile and every access adds a constant
+    // (none is hoisted out of the loop, where they would spill)
+    int ln = tid & 63;
+    if constexpr (kO) asm volatile("" : "+v"(ln));
     // ---- stage 0: operands into LDS (fp32 ones split into hi | lo) ----
     if (!MOM) sx.store(Xh, Xl, ld, tid);
     sy.store(Yh, Yl, ld, tid);
@@ -239,31 +244,31 @@ __device__ __forceinline__ void la_pass(
           f32x16 a = zero16();
 #pragma unroll
           for (int s = 0; s < D / 16; ++s) {
-            const bf16x8 yh = frag<kO>(Yh, ld, kt * 32, s * 16), xh = frag<kO>(Xh, ld, qt * 32, s * 16);
+            const bf16x8 yh = frag<kO>(Yh, ld, kt * 32, s * 16, ln), xh = frag<kO>(Xh, ld, qt * 32, s * 16, ln);
             a = mfma(yh, xh, a);
-            if (XF) a = mfma(yh, frag<kO>(Xl, ld, qt * 32, s * 16), a);
-            if (YF) a = mfma(frag<kO>(Yl, ld, kt * 32, s * 16), xh, a);
+            if (XF) a = mfma(yh, frag<kO>(Xl, ld, qt * 32, s * 16, ln), a);
+            if (YF) a = mfma(frag<kO>(Yl, ld, kt * 32, s * 16, ln), xh, a);
           }
 #pragma unroll
           for (int e = 0; e < 16; ++e) {   // keep key <= query (causal) or key >= query (anti-causal)
             const int key = kt * 32 + acc_row(e, lg), qry = qt * 32 + lr;
             if (rev ? key < qry : key > qry) a[e] = 0.f;
           }
-          store_T<kO>(a, Ah, Al, ldA, kt * 32, qt * 32);
+          store_T<kO>(a, Ah, Al, ldA, kt * 32, qt * 32, ln);
           if constexpr (TWO) {            // A2 = X Z^T on the same tile, z split
             f32x16 a2 = zero16();
 #pragma unroll
             for (int s = 0; s < D / 16; ++s) {
-              const bf16x8 xh = frag<kO>(Xh, ld, qt * 32, s * 16);
-              a2 = mfma(frag<kO>(Zh, ld, kt * 32, s * 16), xh, a2);
-              a2 = mfma(frag<kO>(Zl, ld, kt * 32, s * 16), xh, a2);
+              const bf16x8 xh = frag<kO>(Xh, ld, qt * 32, s * 16, ln);
+              a2 = mfma(frag<kO>(Zh, ld, kt * 32, s * 16, ln), xh, a2);
+              a2 = mfma(frag<kO>(Zl, ld, kt * 32, s * 16, ln), xh, a2);
             }
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
               const int key = kt * 32 + acc_row(e, lg), qry = qt * 32 + lr;
               if (rev ? key < qry : key > qry) a2[e] = 0.f;
             }
-            store_T<kO>(a2, A2h, A2l, ldA, kt * 32, qt * 32);
+            store_T<kO>(a2, A2h, A2l, ldA, kt * 32, qt * 32, ln);
           }
         }
       }
@@ -273,50 +278,50 @@ __device__ __forceinline__ void la_pass(
       for (int j = 0; j < G::KD; ++j) {
         bf16x8 sh, sl;
         frag_from_acc(S0[j >> 1], j & 1, sh, sl);
-        const bf16x8 ah = frag_acc_order<kO>(Xh, ld, rt * 32, j * 16);
+        const bf16x8 ah = frag_acc_order<kO>(Xh, ld, rt * 32, j * 16, ln);
         o = mfma(ah, sh, o);
         o = mfma(ah, sl, o);
-        if (XF) o = mfma(frag_acc_order<kO>(Xl, ld, rt * 32, j * 16), sh, o);
+        if (XF) o = mfma(frag_acc_order<kO>(Xl, ld, rt * 32, j * 16, ln), sh, o);
       }
 #pragma unroll
       for (int s = 0; s < G::KC; ++s) {
         // keys of this k step against the row tile's queries: causal needs s < 2 (rt + 1), anti-causal s >= 2 rt
         if (rev ? s >= 2 * rt : s < 2 * (rt + 1)) {
-          const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16);
-          const bf16x8 ah = frag<kO>(Ah, ldA, rt * 32, s * 16), al = frag<kO>(Al, ldA, rt * 32, s * 16);
+          const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16, ln);
+          const bf16x8 ah = frag<kO>(Ah, ldA, rt * 32, s * 16, ln), al = frag<kO>(Al, ldA, rt * 32, s * 16, ln);
           o = mfma(ah, zh, o);
           o = mfma(al, zh, o);
-          if (ZF) o = mfma(ah, frag_tr<kO>(Zl, ld, ct * 32, s * 16), o);
+          if (ZF) o = mfma(ah, frag_tr<kO>(Zl, ld, ct * 32, s * 16, ln), o);
           if constexpr (TWO) {            // + A2 Y
-            const bf16x8 yh = frag_tr<kO>(Yh, ld, ct * 32, s * 16);
-            o = mfma(frag<kO>(A2h, ldA, rt * 32, s * 16), yh, o);
-            o = mfma(frag<kO>(A2l, ldA, rt * 32, s * 16), yh, o);
+            const bf16x8 yh = frag_tr<kO>(Yh, ld, ct * 32, s * 16, ln);
+            o = mfma(frag<kO>(A2h, ldA, rt * 32, s * 16, ln), yh, o);
+            o = mfma(frag<kO>(A2l, ldA, rt * 32, s * 16, ln), yh, o);
           }
         }
       }
     }
     uint16_t* Oh = Xl;                       // MO: this tile's o, hi | lo
     uint16_t* Ol = MO == 1 ? Yl : Zl;
-    if constexpr (MO != 0) store_N<kO>(o, Oh, Ol, ld, rt * 32, ct * 32);
+    if constexpr (MO != 0) store_N<kO>(o, Oh, Ol, ld, rt * 32, ct * 32, ln);
     // ---- state advance: S0 += Y^T Z (column ct, all rows) ----
 #pragma unroll
     for (int s = 0; s < G::KC; ++s) {
-      const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16);
+      const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16, ln);
       bf16x8 zl;
-      if (ZF) zl = frag_tr<kO>(Zl, ld, ct * 32, s * 16);
+      if (ZF) zl = frag_tr<kO>(Zl, ld, ct * 32, s * 16, ln);
 #pragma unroll
       for (int i = 0; i < ST; ++i) {
-        const bf16x8 yh = frag_tr<kO>(Yh, ld, i * 32, s * 16);
+        const bf16x8 yh = frag_tr<kO>(Yh, ld, i * 32, s * 16, ln);
         S0[i] = mfma(yh, zh, S0[i]);
         if (ZF) S0[i] = mfma(yh, zl, S0[i]);
-        if (YF) S0[i] = mfma(frag_tr<kO>(Yl, ld, i * 32, s * 16), zh, S0[i]);
+        if (YF) S0[i] = mfma(frag_tr<kO>(Yl, ld, i * 32, s * 16, ln), zh, S0[i]);
       }
       if constexpr (TWO) {                // + Z^T Y
-        const bf16x8 yb = frag_tr<kO>(Yh, ld, ct * 32, s * 16);
+        const bf16x8 yb = frag_tr<kO>(Yh, ld, ct * 32, s * 16, ln);
 #pragma unroll
         for (int i = 0; i < ST; ++i) {
-          S0[i] = mfma(frag_tr<kO>(Zh, ld, i * 32, s * 16), yb, S0[i]);
-          S0[i] = mfma(frag_tr<kO>(Zl, ld, i * 32, s * 16), yb, S0[i]);
+          S0[i] = mfma(frag_tr<kO>(Zh, ld, i * 32, s * 16, ln), yb, S0[i]);
+          S0[i] = mfma(frag_tr<kO>(Zl, ld, i * 32, s * 16, ln), yb, S0[i]);
         }
       }
     }
@@ -340,10 +345,10 @@ __device__ __forceinline__ void la_pass(
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int k0 = rt * 32 + s * 16;
-        const bf16x8 oh = frag_tr<kO>(Oh, ld, ct * 32, k0), ol = frag_tr<kO>(Ol, ld, ct * 32, k0);
+        const bf16x8 oh = frag_tr<kO>(Oh, ld, ct * 32, k0, ln), ol = frag_tr<kO>(Ol, ld, ct * 32, k0, ln);
 #pragma unroll
         for (int i = 0; i < SH; ++i) {
-          const bf16x8 a = frag_tr<kO>(Wt, ld, i * 32, k0);
+          const bf16x8 a = frag_tr<kO>(Wt, ld, i * 32, k0, ln);
           M2[i] = mfma(a, oh, M2[i]);
           M2[i] = mfma(a, ol, M2[i]);
         }
