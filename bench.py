@@ -49,6 +49,10 @@ def kernel_costs(w, P=None, tile=None, first=None, per=None, two_pass=False):
         "readout": ("alu", tok * (qkv_tok + 4 * dv) + BH * M * F * 4,
                     tok * 2 * (d * d + 1.5 * C * d + 2 * d * dv + C * dv / 2)),
         "scan": ("hbm", 2 * BH * M * F * 4, BH * M * 2 * (d * d * dv + d * d)),
+        # fp32 / fp64 walk (d = dv, 32-token tiles): its launches' token traffic
+        "walk32": ("hbm", tok * (qkv_tok + 4 * dv), tok * reference_flops_per_token(32, d, dv)),
+        "moments32": ("hbm", tok * (d * es if w["masked"] else qkv_tok), tok * 2 * d * (d if w["masked"] else d + dv)),
+        "fix32": ("hbm", tok * (d * es + 8 * dv), tok * 2 * d * dv),
     }
     if P:
         Ct = tile

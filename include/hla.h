@@ -49,7 +49,8 @@
  *     hla2_workspace_query returns the status itself.
  *   - The environment variable HLA_FUSED_SEGMENTS=<p>, when set, overrides
  *     how many segments per head the segment-walk plans (fused forward and
- *     its decayed form, AHLA, backward, third order) cut each head into, for
+ *     its decayed form, the fp32 / fp64 walk, AHLA, backward, third order)
+ *     cut each head into (fewer where the workspace holds fewer), for
  *     testing and tuning; any p >= 1 gives the same result up to fp32
  *     rounding order.  Workspace queries read it too: set it before the
  *     query.  A call checks its workspace against its own plan.
@@ -82,7 +83,8 @@ typedef enum { HLA_FP32 = 0, HLA_BF16 = 1 } hla_dtype;
 /* Forward algorithms selectable through hla2_forward_ex. */
 typedef enum {
   HLA_ALGO_AUTO = 0,     /* library choice (fused when supported)             */
-  HLA_ALGO_CHUNKED = 1,  /* per-chunk summaries, (+)-scan, per-chunk readout  */
+  HLA_ALGO_CHUNKED = 1,  /* fp32 / fp64 arithmetic: a segment walk (d = dv),
+                            else per-chunk summaries, (+)-scan, readout       */
   HLA_ALGO_FUSED = 2     /* segment walk with the carry state kept on chip    */
 } hla_algo;
 

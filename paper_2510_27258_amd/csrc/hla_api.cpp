@@ -12,6 +12,7 @@
 #include "fused.h"
 #include "hla3.h"
 #include "profile.h"
+#include "walk32.h"
 
 namespace {
 
@@ -154,6 +155,11 @@ int hla2_forward_ex(const void* q, const void* k, const void* v, float* out, flo
   const size_t need = chunked_ws(BH, n, d, dv, chunk);
   if (!workspace || workspace_bytes < need)
     return fail(HLA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+  if (hla::walk32_supported(f)) {
+    const hipError_t e = hla::launch_walk32(f, workspace, need, s);
+    if (e != hipSuccess) return hip_fail(e, "forward walk");
+    return ok();
+  }
   f.chunk = path_chunk(chunk);
   const int M = (n + f.chunk - 1) / f.chunk;
   float* states = static_cast<float*>(workspace);
@@ -244,6 +250,11 @@ int hla2_forward_decay(const void* q, const void* k, const void* v, float* out, 
     return fail(HLA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
   const int cc = path_chunk(chunk);
   hla::Fwd f{q, k, v, out, BH, n, d, dv, cc, masked, normalized, dtype, eps, gamma};
+  if (hla::walk32_supported(f)) {
+    const hipError_t e = hla::launch_walk32(f, workspace, need, s);
+    if (e != hipSuccess) return hip_fail(e, "forward walk");
+    return ok();
+  }
   const int M = (n + cc - 1) / cc;
   const int last = n - (M - 1) * cc;
   const float rho = (float)std::pow((double)gamma, (double)cc), rho_last = (float)std::pow((double)gamma, (double)last);
