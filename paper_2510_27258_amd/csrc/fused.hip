@@ -1073,45 +1073,10 @@ bool legacy_pipeline() {
   return e && e[0] == '1';
 }
 
-// Per-tile time of the summary walk over that of the output walk (both at
-// one workgroup per CU, d = dv = 128: about 3.9 and 6.6 us per tile).
-constexpr double kWsSummaryRatio = 0.65;
-
 // Segments per head up to which the row-split walk (no initial state) sums
 // its S prefix from the moments itself instead of reading it from a prefix
 // launch.
 constexpr int kWalkSumMax = 8;
-
-// Segments of the two-pass plan: with Q = 256 / BH walks per head in each
-// launch (one workgroup per CU), segments 1 .. P-1 get x tiles each (the
-// last the rest) and segment 0 about r x, r the ratio above, so that segment
-// 0's output walk and the summary walks beside it end together.  With fewer
-// than two later segments the plan is a single output walk per head.
-void ws_plan(int BH, int n, int* P, int* cps, int* c0) {
-  const int M = (n + CfgWS::C - 1) / CfgWS::C;
-  int Q = 256 / BH;
-  if (const char* e = getenv("HLA_FUSED_SEGMENTS")) Q = atoi(e) - 1;
-  double r = kWsSummaryRatio;
-  if (const char* e = getenv("HLA_WS_RATIO")) r = atof(e);
-  if (Q >= 2 && M >= 3 && r > 0.0) {
-    int x = (int)ceil(M / (Q + r));
-    const int l0 = std::max(1, (int)lround(r * x));
-    if (l0 < M) {
-      const int rest = M - l0;
-      if ((rest + x - 1) / x > Q) x = (rest + Q - 1) / Q;
-      const int p1 = (rest + x - 1) / x;
-      if (p1 >= 2) {
-        *P = 1 + p1;
-        *cps = x;
-        *c0 = l0;
-        return;
-      }
-    }
-  }
-  *P = 1;
-  *cps = M;
-  *c0 = M;
-}
 
 hipError_t launch_ws(const void* fn, dim3 grid, hipStream_t s, void** args) {
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CfgWS::bytes);
@@ -1195,12 +1160,19 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
     if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
     // the S prefixes of segments 1 .. P-1 and the brackets of 1 .. P-2 (no
     // walk writes record P - 1: the sums that include it are never stored)
+    const int summed = P > kBracketSumMax;
+    if (summed) {
+      prof_start("seg_prefix", s);
+      HLA_LAUNCH(k_seg_prefix, seg_prefix_grid(D * D, BH), dim3(256), 0, s, segs, F, 0, D * D, 0, spre, P, 1.f);
+      prof_stop(s);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     prof_start("bracket", s);
-    HLA_LAUNCH((k_ws_bracket<D, DV>), dim3(P - 1, BH), dim3(1024), 0, s, segs, spre, P);
+    HLA_LAUNCH((k_ws_bracket<D, DV>), dim3(P - 1, BH), dim3(1024), 0, s, segs, spre, P, summed);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     prof_start("seg_prefix", s);
-    HLA_LAUNCH(k_seg_prefix, dim3((D * DV + D + 1023) / 1024, BH), dim3(256), 0, s, segs, F, (int)off_G(D, DV),
+    HLA_LAUNCH(k_seg_prefix, seg_prefix_grid(D * DV + D, BH), dim3(256), 0, s, segs, F, (int)off_G(D, DV),
                D * DV + D, 0, carry, P, 1.f);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1257,7 +1229,7 @@ hipError_t run_shape(const Fwd& f, float* state, float* total, char* ws, int P, 
     spre = reinterpret_cast<float*>(ws + legacy_spre_offset(BH, f.n, P, C, D, DV));
     const float rhoS = DEC ? (float)std::exp2((double)lg2g * (double)C * (double)cps) : 1.f;
     prof_start("seg_prefix", s);
-    HLA_LAUNCH(k_seg_prefix, dim3((D * D + 1023) / 1024, BH), dim3(256), 0, s, segs, state_floats(D, DV), 0, D * D,
+    HLA_LAUNCH(k_seg_prefix, seg_prefix_grid(D * D, BH), dim3(256), 0, s, segs, state_floats(D, DV), 0, D * D,
                state ? 1 : 0, spre, P, rhoS);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -124,3 +124,23 @@ def test_ahla_errors():
     torch.cuda.synchronize()
     assert bool((out == 7.0).all()), "a rejected call wrote its output"
     assert capi.ahla_workspace_bytes(1, 1, 64, 32, 32, 64, I.HLA_BF16) == 0
+
+
+@pytest.mark.parametrize("normalized", [0, 1])
+@pytest.mark.parametrize("n,segments", [(1, 0), (64, 0), (193, 4), (1500, 9), (1500, 17), (901, 0)])
+def test_ahla_two_pass_d128(n, segments, normalized, monkeypatch):
+    """d = 128: one output walk, the two passes with the prefixes summed by the
+    bracket launch (up to 12 segments) and by their own (more), ragged tails."""
+    if segments:
+        monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    _check(1, 3, n, 128, 128, normalized=bool(normalized), seed=21)
+
+
+@pytest.mark.parametrize("segments", [13, 24])
+def test_forward_two_pass_many_segments(segments, monkeypatch):
+    """The second-order walk at d = 128 with the S prefixes from their own launch."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    q, k, v, code = gen(1, 2, 1900, 128, 128, "unit", 5)
+    num, _, _, _ = native.hla2_serial_c(q, k, v, masked=True, threads=4)
+    out = hla.forward(dev(q, code), dev(k, code), dev(v, code), 128).cpu().numpy()
+    assert rowwise_err(out, num) <= tol_for(code)
