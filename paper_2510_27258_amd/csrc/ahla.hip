@@ -26,11 +26,13 @@
 //   3. k_carry / k_fix: running sums of the brackets are the E and n carries
 //      of the segments; out_t += q_t^T E_c, den_t += q_t . (n0 + n_c).
 //
-// This is the d = 64 form; d = 128 takes the two-pass plan of ahla_ws.h.
-//
-// Layout: wave w owns row tile w / NCT and column tile ct = w % NCT of the
-// output and keeps column ct of P0 and E0 (all d rows) in MFMA accumulators;
-// the two row waves of a column both keep it, so no partial sums are exchanged.
+// Layout: wave w owns column tile ct = w % NCT of the output for RPW row
+// tiles (from row tile (w / NCT) RPW), and keeps column ct of P0 and E0 (all
+// d rows) in MFMA accumulators.  At d = 64 (RPW = 1) the two row waves of a
+// column both keep it, so no partial sums are exchanged; at d = 128 (RPW = 2)
+// four waves, one per SIMD, each keep one column (the state once, with up to
+// 512 registers a wave: two row waves per column spilled 152 bytes a lane).
+// Longer calls at d = 128 take the two-pass plan of ahla_ws.h (ahla_two_pass).
 // Numerics as in the second-order walk: q, k, v exact in bf16; every computed
 // operand (A, R, P0, E0) split into bf16 hi + lo, fp32 accumulation.
 #include <cstdlib>
@@ -46,7 +48,7 @@ namespace {
 template <int D>
 struct CfgAH {
   static constexpr int C = 64, DV = D;
-  static constexpr int NCT = D / 32, NW = 2 * NCT, NT = 64 * NW;
+  static constexpr int NCT = D / 32, RPW = D == 128 ? 2 : 1, NW = 2 * NCT / RPW, NT = 64 * NW;
   static constexpr int ST = D / 32, KC = C / 16, KD = D / 16;
   static constexpr int ldQ = D + kPad, ldK = D + kPad, ldV = DV + kPad, ldW = C + kPad, ldR = C + kPad;
   static constexpr int oQ = 0;
@@ -58,7 +60,7 @@ struct CfgAH {
   static constexpr int oRl = oRh + DV * ldR;
   static constexpr int n16 = oRl + DV * ldR;
   static constexpr int oX = oQ;                // output staging, over Q | V once both are dead
-  static_assert(NW * 1024 * 2 <= oK - oQ, "output staging fits Q | V");
+  static_assert(NW * RPW * 1024 * 2 <= oK - oQ, "output staging fits Q | V");
   static_assert(D * DV * 2 <= n16, "carry staging fits the tile region");
   static constexpr int f_m = 0, f_n = D, f_rs = 2 * D, f_s = 2 * D + 2 * C;
   static constexpr int nf32 = f_s + C;
@@ -66,19 +68,20 @@ struct CfgAH {
   static constexpr int kBlocks = 2 * bytes <= 160 * 1024 && NW <= 4 ? 2 : 1;
   static constexpr int pfQ = C * D / 8 / NT, pfV = C * DV / 8 / NT;
   static_assert(C * D / 8 % NT == 0 && C * DV / 8 % NT == 0 && pfQ >= 1, "staging");
-  static_assert(D == 64, "d = 128 takes the wave-specialised walk");
+  static_assert(D == 64 || D == 128, "AHLA walk shapes");
   static_assert(bytes <= 160 * 1024, "LDS budget");
   static_assert(NT >= D + C, "den lanes and state lanes are distinct");
 };
 
 template <int D>
 __global__ __launch_bounds__((CfgAH<D>::NT), (CfgAH<D>::kBlocks))
-__attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
+__attribute__((amdgpu_waves_per_eu(CfgAH<D>::RPW == 2 ? 1 : 2))) void k_ahla_walk(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ out, float* __restrict__ den_out, float* __restrict__ rec, const float* __restrict__ ppre,
     int n, int cps, int nseg, int normalized) {
   using G = CfgAH<D>;
-  constexpr int C = G::C, DV = G::DV, NT = G::NT, ST = G::ST;
+  constexpr bool kO = D == 128;     // per-tile opaque lane index (registers)
+  constexpr int C = G::C, DV = G::DV, NT = G::NT, ST = G::ST, RPW = G::RPW;
   extern __shared__ __align__(16) uint16_t lds[];
   uint16_t* Qs = lds + G::oQ;
   uint16_t* Vs = lds + G::oV;
@@ -98,7 +101,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
   seg_head(seg, bh);
   const int tid = threadIdx.x, l = tid & 63, lr = l & 31, lg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rt = w / G::NCT, ct = w % G::NCT;   // this wave's row and column tile
+  const int rtb = (w / G::NCT) * RPW, ct = w % G::NCT;   // row tiles rtb .. rtb + RPW - 1
   const int M = (n + C - 1) / C;
   const int c_begin = seg * cps, c_end = min(M, c_begin + cps);
   const size_t F = state_floats(D, DV);
@@ -174,11 +177,13 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
   const rsrc_t rk = make_rsrc(k + (size_t)bh * n * D, (uint32_t)n * D * 2);
   const rsrc_t rv = make_rsrc(v + (size_t)bh * n * DV, (uint32_t)n * DV * 2);
   uint4 pq[G::pfQ], pk[G::pfQ], pv[G::pfV];
-  // 16-byte piece e of a C x W tile: token pt, first column pc;
+  // 16-byte piece e of a C x W tile: token pt, first column pc.  At d = 64
   // consecutive lanes take consecutive pieces of a token row (coalesced
-  // loads, contiguous LDS stores).
-  auto pt = [](int e, int W) { return e / (W / 8); };
-  auto pc = [](int e, int W) { return (e % (W / 8)) * 8; };
+  // loads, contiguous LDS stores); at d = 128 consecutive tokens, which
+  // measured faster for this walk there.
+  constexpr bool RP = D <= 64;
+  auto pt = [](int e, int W) { return RP ? e / (W / 8) : e % C; };
+  auto pc = [](int e, int W) { return RP ? (e % (W / 8)) * 8 : (e / C) * 8; };
   auto fetch = [&](int c) {
     const uint32_t t0 = (uint32_t)c * C;
 #pragma unroll
@@ -198,7 +203,11 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
 
   for (int c = c_begin; c < c_end; ++c) {
     const int t0 = c * C;
-    const int ln = tid & 63;
+    // lane index for the fragment helpers, opaque once per tile at d = 128:
+    // lane offsets are formed once per tile and no address is hoisted out of
+    // the walk
+    int ln = tid & 63;
+    if constexpr (kO) asm volatile("" : "+v"(ln));
     // ---- stage 0: registers -> LDS, row-major (transposed operands go through the transpose unit) ----
 #pragma unroll
     for (int i = 0; i < G::pfQ; ++i) {
@@ -223,7 +232,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
         f32x16 acc = zero16();
 #pragma unroll
         for (int s = 0; s < D / 16; ++s)
-          acc = mfma(frag(Ks, G::ldK, it * 32, s * 16, ln), frag(Qs, G::ldQ, jt * 32, s * 16, ln), acc);
+          acc = mfma(frag<kO>(Ks, G::ldK, it * 32, s * 16, ln), frag<kO>(Qs, G::ldQ, jt * 32, s * 16, ln), acc);
 #pragma unroll
         for (int e = 0; e < 16; ++e)   // keep key i <= query t
           if (it * 32 + acc_row(e, lg) > jt * 32 + lr) acc[e] = 0.f;
@@ -234,7 +243,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
           ps += __shfl_xor(ps, 32);
           if (lg == 0) rs[it * C + jt * 32 + lr] = ps;
         }
-        store_T(acc, Wh, Wl, G::ldW, it * 32, jt * 32, ln);
+        store_T<kO>(acc, Wh, Wl, G::ldW, it * 32, jt * 32, ln);
       } else if (normalized && lg == 0) {
         rs[it * C + jt * 32 + lr] = 0.f;
       }
@@ -259,29 +268,40 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
     }
 
     // ---- stage 2: R = Q P0 + A V and the O partial Q E0 (old carries); P0 += K^T V ----
-    f32x16 racc = zero16(), oacc = zero16();
+    f32x16 racc[RPW], oacc[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+      racc[r] = zero16();
+      oacc[r] = zero16();
+    }
 #pragma unroll
     for (int j = 0; j < G::KD; ++j) {
       bf16x8 ph, pl, eh, el;
       frag_from_acc(P0[j >> 1], j & 1, ph, pl);
       frag_from_acc(E0[j >> 1], j & 1, eh, el);
-      const bf16x8 aQ = frag_acc_order(Qs, G::ldQ, rt * 32, j * 16, ln);
-      racc = mfma(aQ, ph, racc);
-      racc = mfma(aQ, pl, racc);
-      oacc = mfma(aQ, eh, oacc);
-      oacc = mfma(aQ, el, oacc);
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) {
+        const bf16x8 aQ = frag_acc_order<kO>(Qs, G::ldQ, (rtb + r) * 32, j * 16, ln);
+        racc[r] = mfma(aQ, ph, racc[r]);
+        racc[r] = mfma(aQ, pl, racc[r]);
+        oacc[r] = mfma(aQ, eh, oacc[r]);
+        oacc[r] = mfma(aQ, el, oacc[r]);
+      }
     }
 #pragma unroll
     for (int s = 0; s < G::KC; ++s) {
-      const bf16x8 bV = frag_tr(Vs, G::ldV, ct * 32, s * 16, ln);
-      if (s < 2 * (rt + 1)) {    // keys past the row tile: A is zero
-        racc = mfma(frag(Wh, G::ldW, rt * 32, s * 16, ln), bV, racc);
-        racc = mfma(frag(Wl, G::ldW, rt * 32, s * 16, ln), bV, racc);
-      }
+      const bf16x8 bV = frag_tr<kO>(Vs, G::ldV, ct * 32, s * 16, ln);
 #pragma unroll
-      for (int i = 0; i < ST; ++i) P0[i] = mfma(frag_tr(Ks, G::ldK, i * 32, s * 16, ln), bV, P0[i]);
+      for (int r = 0; r < RPW; ++r)
+        if (s < 2 * (rtb + r + 1)) {    // keys past the row tile: A is zero
+          racc[r] = mfma(frag<kO>(Wh, G::ldW, (rtb + r) * 32, s * 16, ln), bV, racc[r]);
+          racc[r] = mfma(frag<kO>(Wl, G::ldW, (rtb + r) * 32, s * 16, ln), bV, racc[r]);
+        }
+#pragma unroll
+      for (int i = 0; i < ST; ++i) P0[i] = mfma(frag_tr<kO>(Ks, G::ldK, i * 32, s * 16, ln), bV, P0[i]);
     }
-    store_T(racc, Rh, Rl, G::ldR, rt * 32, ct * 32, ln);   // R^T
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) store_T<kO>(racc[r], Rh, Rl, G::ldR, (rtb + r) * 32, ct * 32, ln);   // R^T
     lds_barrier();                      // R^T and s visible; Q and V are dead
 
     // ---- normalised: den partial (A s)_t, the tile's n0, then m0 and n0 advance ----
@@ -320,32 +340,37 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
     // ---- stage 3: E0 += K^T R;  O += A R (A and R both split: hi hi, hi lo, lo hi) ----
 #pragma unroll
     for (int s = 0; s < G::KC; ++s) {
-      const bf16x8 brh = frag(Rh, G::ldR, ct * 32, s * 16, ln);
-      const bf16x8 brl = frag(Rl, G::ldR, ct * 32, s * 16, ln);
+      const bf16x8 brh = frag<kO>(Rh, G::ldR, ct * 32, s * 16, ln);
+      const bf16x8 brl = frag<kO>(Rl, G::ldR, ct * 32, s * 16, ln);
 #pragma unroll
       for (int i = 0; i < ST; ++i) {
-        const bf16x8 aK = frag_tr(Ks, G::ldK, i * 32, s * 16, ln);
+        const bf16x8 aK = frag_tr<kO>(Ks, G::ldK, i * 32, s * 16, ln);
         E0[i] = mfma(aK, brh, E0[i]);
         E0[i] = mfma(aK, brl, E0[i]);
       }
-      if (s < 2 * (rt + 1)) {
-        const bf16x8 awh = frag(Wh, G::ldW, rt * 32, s * 16, ln);
-        const bf16x8 awl = frag(Wl, G::ldW, rt * 32, s * 16, ln);
-        oacc = mfma(awh, brh, oacc);
-        oacc = mfma(awh, brl, oacc);
-        oacc = mfma(awl, brh, oacc);
-      }
+#pragma unroll
+      for (int r = 0; r < RPW; ++r)
+        if (s < 2 * (rtb + r + 1)) {
+          const bf16x8 awh = frag<kO>(Wh, G::ldW, (rtb + r) * 32, s * 16, ln);
+          const bf16x8 awl = frag<kO>(Wl, G::ldW, (rtb + r) * 32, s * 16, ln);
+          oacc[r] = mfma(awh, brh, oacc[r]);
+          oacc[r] = mfma(awh, brl, oacc[r]);
+          oacc[r] = mfma(awl, brh, oacc[r]);
+        }
     }
     // the output tiles go through this wave's staging slots so that each lane
     // stores 16 bytes; rows past n fall outside the buffer and are dropped
-    float* ob = XO + w * 1024;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) ob[acc_row(e, lg) * 32 + lr] = oacc[e];
+    for (int r = 0; r < RPW; ++r) {
+      float* ob = XO + (w * RPW + r) * 1024;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int p = l + 64 * j, row = p >> 3, c4 = (p & 7) * 4;
-      buf_store16(ro, (((uint32_t)t0 + rt * 32 + row) * DV + ct * 32 + c4) * 4,
-                  *reinterpret_cast<const float4*>(ob + row * 32 + c4));
+      for (int e = 0; e < 16; ++e) ob[acc_row(e, lg) * 32 + lr] = oacc[r][e];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int p = l + 64 * j, row = p >> 3, c4 = (p & 7) * 4;
+        buf_store16(ro, (((uint32_t)t0 + (rtb + r) * 32 + row) * DV + ct * 32 + c4) * 4,
+                    *reinterpret_cast<const float4*>(ob + row * 32 + c4));
+      }
     }
     lds_barrier();   // every LDS tile is rewritten by the next chunk
   }
@@ -354,7 +379,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
   // other row waves hold the same columns), n0 into the h slot
   int col = ct * 32 + lr;
   asm volatile("" : "+v"(col));
-  if (rt == 0) {
+  if (rtb == 0) {
 #pragma unroll
     for (int i = 0; i < ST; ++i)
 #pragma unroll
@@ -364,9 +389,9 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_ahla_walk(
 }
 
 // Segments: enough walks to fill the chip (workgroups per CU times 256 CUs).
-void ahla_plan(int BH, int n, int* P, int* cps) {
+void ahla_plan(int D, int BH, int n, int* P, int* cps) {
   const int M = (n + 63) / 64;
-  const int blocks = CfgAH<64>::kBlocks;
+  const int blocks = D == 64 ? CfgAH<64>::kBlocks : CfgAH<128>::kBlocks;
   int p = 256 * blocks / BH;
   if (const char* e = getenv("HLA_FUSED_SEGMENTS")) p = atoi(e);
   if (p < 1) p = 1;
@@ -498,6 +523,21 @@ hipError_t run_ahla_ws(const Fwd& f, char* ws, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether a call takes the two-pass plan of ahla_ws.h: d = 128, and either one
+// walk a head without a first pass, or at least four tiles a segment, or many
+// segments.  Below that its two walks and two launches between them cost more
+// than the moments, carry and fix-up launches of one walk from the P prefix
+// (us, one pass / two passes): 1 tile a segment, 16 segments, 16 heads of 1000
+// 49 / 62, 4 heads 40 / 44; 3 tiles, 36 heads of 1000 60 / 67, 128 of 400
+// 62 / 70; but 7 tiles, 128 heads of 1000 122 / 113; 47 segments, 4 heads of 3000
+// 63 / 57; one walk, 128 heads of 100 tokens 36 / 14.
+bool ahla_two_pass(int BH, int n, int d) {
+  if (d != CfgAW::D) return false;
+  int P, cps, c0;
+  ws_plan(BH, n, &P, &cps, &c0);
+  return P == 1 || cps >= 4 || P > 24;
+}
+
 }  // namespace
 
 bool ahla_supported(int n, int d, int dv, int chunk, int dtype) {
@@ -508,22 +548,22 @@ bool ahla_supported(int n, int d, int dv, int chunk, int dtype) {
 
 size_t ahla_workspace_bytes(int BH, int n, int d) {
   int P, cps;
-  if (d == CfgAW::D) {
+  if (ahla_two_pass(BH, n, d)) {
     int c0;
     ws_plan(BH, n, &P, &cps, &c0);
     return ahla_ws_bytes(BH, P, d) + 256;
   }
-  ahla_plan(BH, n, &P, &cps);
+  ahla_plan(d, BH, n, &P, &cps);
   return records_bytes_ah(BH, P, d) + den_bytes_ah(BH, n, d) + 2 * carry_bytes_ah(BH, P, d) + 256;
 }
 
 hipError_t launch_ahla(const Fwd& f, void* workspace, hipStream_t s) {
   if (!ahla_supported(f.n, f.d, f.dv, f.chunk, f.dtype)) return hipErrorNotSupported;
   char* ws = static_cast<char*>(workspace);
-  if (f.d == CfgAW::D) return run_ahla_ws(f, ws, s);
+  if (ahla_two_pass(f.BH, f.n, f.d)) return run_ahla_ws(f, ws, s);
   int P, cps;
-  ahla_plan(f.BH, f.n, &P, &cps);
-  return run_ahla<64>(f, ws, P, cps, s);
+  ahla_plan(f.d, f.BH, f.n, &P, &cps);
+  return f.d == 64 ? run_ahla<64>(f, ws, P, cps, s) : run_ahla<128>(f, ws, P, cps, s);
 }
 
 }  // namespace hla

@@ -126,11 +126,13 @@ def test_ahla_errors():
     assert capi.ahla_workspace_bytes(1, 1, 64, 32, 32, 64, I.HLA_BF16) == 0
 
 
-@pytest.mark.parametrize("normalized", [0, 1])
-@pytest.mark.parametrize("n,segments", [(1, 0), (64, 0), (193, 4), (1500, 9), (1500, 17), (901, 0)])
+@pytest.mark.parametrize("n,segments,normalized", [
+    (1, 0, 0), (64, 0, 1), (193, 4, 1), (1500, 5, 0), (1500, 5, 1), (1700, 27, 1), (901, 0, 1),
+    (3600, 14, 0)])     # unnormalised: too few rows keep a denominator away from 0 at this length
 def test_ahla_two_pass_d128(n, segments, normalized, monkeypatch):
-    """d = 128: one output walk, the two passes with the prefixes summed by the
-    bracket launch (up to 12 segments) and by their own (more), ragged tails."""
+    """d = 128: one output walk, one pass (193), the two passes with the
+    prefixes summed by the bracket launch (up to 12 segments) and by their own
+    (more), many segments, ragged tails."""
     if segments:
         monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
     _check(1, 3, n, 128, 128, normalized=bool(normalized), seed=21)
