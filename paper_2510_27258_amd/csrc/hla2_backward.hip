@@ -272,8 +272,9 @@ __device__ __forceinline__ void la_pass(
           }
         }
       }
-      lds_barrier();
-      // ---- stage 2: O = X S0 (state before this tile) + A Z ----
+      // ---- O = X S0 (state before this tile): here, where the waves without
+      // a tile of A would wait for it (B1H8 n16384 d = 128: 476 -> 459 us; the
+      // state advance here as well made the waves with one later: 567 us) ----
 #pragma unroll
       for (int j = 0; j < G::KD; ++j) {
         bf16x8 sh, sl;
@@ -283,6 +284,10 @@ __device__ __forceinline__ void la_pass(
         o = mfma(ah, sl, o);
         if (XF) o = mfma(frag_acc_order<kO>(Xl, ld, rt * 32, j * 16, ln), sh, o);
       }
+    }
+    if (!MOM) {
+      // ---- stage 2: O += A Z ----
+      lds_barrier();
 #pragma unroll
       for (int s = 0; s < G::KC; ++s) {
         // keys of this k step against the row tile's queries: causal needs s < 2 (rt + 1), anti-causal s >= 2 rt
