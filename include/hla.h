@@ -326,6 +326,13 @@ int hla2_backward(const void *q, const void *k, const void *v, const float *g, f
                   float *dv, int B, int H, int n, int d, int dv_dim, int chunk, int dtype,
                   void *workspace, size_t workspace_bytes, void *stream);
 
+/* As hla2_backward with the gradients in grad_dtype: HLA_FP32, or HLA_BF16 for
+ * dq, dk, dv bf16 (the same fp32 sums, rounded to nearest even once). */
+size_t hla2_backward_workspace_bytes_ex(int B, int H, int n, int d, int dv, int chunk, int dtype, int grad_dtype);
+int hla2_backward_ex(const void *q, const void *k, const void *v, const float *g, void *dq, void *dk,
+                     void *dv, int B, int H, int n, int d, int dv_dim, int chunk, int dtype, int grad_dtype,
+                     void *workspace, size_t workspace_bytes, void *stream);
+
 /* ---------------------------------------------------------------------------
  * ahla_forward — asymmetric second-order HLA (AHLA, Sec. 6): the left-cascaded
  * product ((A A) (.) L) V with A = L (.) Q K^T (diagonal kept),

@@ -101,7 +101,7 @@ template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO =
 __device__ __forceinline__ void la_pass(
     const void* __restrict__ xp, const void* __restrict__ yp, const void* __restrict__ zp, float* __restrict__ out,
     float* __restrict__ rec, int n, int cps, int nseg, int rev, int acc_out, int tr, int scanned,
-    const void* __restrict__ wp, float* __restrict__ rec2, int seg, int bh) {
+    const void* __restrict__ wp, float* __restrict__ rec2, uint16_t* __restrict__ out16, int seg, int bh) {
   using G = CfgLA<D>;
   static_assert(!TWO || (!XF && !YF && !MOM), "the paired pass keeps A2 in the lo tiles of x and y");
   // MO: the walk also forms its segment's moments sum w o^T of its own output
@@ -140,7 +140,7 @@ __device__ __forceinline__ void la_pass(
   const rsrc_t rx = make_rsrc(static_cast<const char*>(xp) + (size_t)bh * n * D * eX, (uint32_t)(n * D * eX));
   const rsrc_t ry = make_rsrc(static_cast<const char*>(yp) + (size_t)bh * n * D * eY, (uint32_t)(n * D * eY));
   const rsrc_t rz = make_rsrc(static_cast<const char*>(zp) + (size_t)bh * n * D * eZ, (uint32_t)(n * D * eZ));
-  const rsrc_t ro = make_rsrc(MOM ? nullptr : out + (size_t)bh * n * D, MOM ? 0u : (uint32_t)n * D * 4);
+  const rsrc_t ro = make_rsrc(MOM || !out ? nullptr : out + (size_t)bh * n * D, MOM || !out ? 0u : (uint32_t)n * D * 4);
   Stage<D, NT, XF> sx;
   Stage<D, NT, YF> sy;
   Stage<D, NT, ZF> sz;
@@ -339,8 +339,24 @@ __device__ __forceinline__ void la_pass(
         prev[e] = acc_out ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
                                 ro, (int)(ob + (8 * (e >> 2) + (e & 3)) * D * 4), 0, 0))
                           : 0.f;
+      if (out16) {
+        // bf16 rows: two lanes share a pair of columns, the even one storing
+        // row e and the odd one row e + 1, four bytes each
+        const rsrc_t r16 = make_rsrc(out16 + (size_t)bh * n * D, (uint32_t)n * D * 2);
+        const int odd = ln & 1;
+        const uint32_t ob16 = (((uint32_t)c * C + rt * 32 + 4 * lg + odd) * D + ct * 32 + (lr & ~1)) * 2;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) buf_store4(ro, ob + (8 * (e >> 2) + (e & 3)) * D * 4, prev[e] + o[e]);
+        for (int e = 0; e < 16; e += 2) {
+          const float x0 = prev[e] + o[e], x1 = prev[e + 1] + o[e + 1];
+          const float y = __shfl_xor(odd ? x0 : x1, 1);
+          const float a = odd ? y : x0, b = odd ? x1 : y;
+          const uint32_t v = pack2(bf16_bits((__bf16)a), bf16_bits((__bf16)b));
+          __builtin_amdgcn_raw_buffer_store_b32(v, r16, (int)(ob16 + (8 * (e >> 2) + (e & 3)) * D * 2), 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) buf_store4(ro, ob + (8 * (e >> 2) + (e & 3)) * D * 4, prev[e] + o[e]);
+      }
     }
     if constexpr (MO != 0) {
       // M2 += w^T o over this wave's 32 tokens: the o piece read back is the
@@ -406,12 +422,13 @@ struct LaArgs {
   int n, cps, nseg, rev, acc_out, tr, scanned;
   const void* wp;
   float* rec2;
+  uint16_t* out16;   // not null: the result (out, with acc_out, plus this pass) goes here rounded to bf16
 };
 template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO = 0>
 struct LaPass {
   static __device__ __forceinline__ void run(const LaArgs& a, int seg, int bh) {
     la_pass<D, XF, YF, ZF, MOM, TWO, MO>(a.xp, a.yp, a.zp, a.out, a.rec, a.n, a.cps, a.nseg, a.rev, a.acc_out, a.tr,
-                                         a.scanned, a.wp, a.rec2, seg, bh);
+                                         a.scanned, a.wp, a.rec2, a.out16, seg, bh);
   }
 };
 
@@ -522,8 +539,8 @@ hipError_t la_launch(const char* name, const LaArgs& a0, const LaArgs& a1, const
 // The arguments of a pass LA(x, y, z) (rev: anti-causal; acc: add to out;
 // tr: the records hold the transposed moments).
 LaArgs la_args(const void* x, const void* y, const void* z, float* out, float* rec, int n, int cps, int P, int rev,
-               int acc, int tr, const void* wp = nullptr, float* rec2 = nullptr) {
-  return LaArgs{x, y, z, out, rec, n, cps, P, rev, acc, tr, P > kScanAbove ? 1 : 0, wp, rec2};
+               int acc, int tr, const void* wp = nullptr, float* rec2 = nullptr, uint16_t* out16 = nullptr) {
+  return LaArgs{x, y, z, out, rec, n, cps, P, rev, acc, tr, P > kScanAbove ? 1 : 0, wp, rec2, out16};
 }
 
 size_t rec_bytes(int BH, int P, int d) {
@@ -546,6 +563,13 @@ hipError_t run_backward(const Bwd& b, char* ws, hipStream_t s) {
   float* qu = reinterpret_cast<float*>(ws + 3 * rb);
   float* r = reinterpret_cast<float*>(ws + 4 * rb);
   float* u = reinterpret_cast<float*>(ws + 4 * rb + vec_bytes(BH, n, D));
+  // bf16 gradients: dv and dk are written rounded by their only pass, dq by
+  // its second, which reads the first term from the workspace in fp32
+  const bool g16 = b.grad_dtype == 1;
+  float* dq = g16 ? u + vec_bytes(BH, n, D) / 4 : static_cast<float*>(b.dq);
+  float* dk = g16 ? nullptr : static_cast<float*>(b.dk);
+  float* dv = g16 ? nullptr : static_cast<float*>(b.dv);
+  auto h16 = [&](void* p) { return g16 ? static_cast<uint16_t*>(p) : nullptr; };
   hipError_t e;
 #define HLA_TRY(x) if ((e = (x)) != hipSuccess) return e
   // Each moment set serves walks of one direction only, so with many
@@ -576,11 +600,13 @@ hipError_t run_backward(const Bwd& b, char* ws, hipStream_t s) {
   // the first dq term LA+(g, v, r), beside dv = LA-(r, q, g) (moments q^T g =
   // (g^T q)^T) and dk = LA-(k, q, u) + LA-(k, u, q) in one paired walk (state
   // sum q u^T + u q^T); then the second dq term LA+(u, k, k), added
-  HLA_TRY((la_launch<D, 3, WalkG, WalkG, WalkK>("bwd_dq_dv_dk", la_args(b.g, b.v, r, b.dq, vr, n, cps, P, 0, 0, 0),
-                                                la_args(r, b.q, b.g, b.dv, gq, n, cps, P, 1, 0, 1),
-                                                la_args(b.k, b.q, u, b.dk, qu, n, cps, P, 1, 0, 0), BH, P, s)));
-  HLA_TRY((la_launch<D, 1, WalkU2>("bwd_dq", la_args(u, b.k, b.k, b.dq, kk, n, cps, P, 0, 1, 0), none, none, BH, P,
-                                   s)));
+  HLA_TRY((la_launch<D, 3, WalkG, WalkG, WalkK>("bwd_dq_dv_dk", la_args(b.g, b.v, r, dq, vr, n, cps, P, 0, 0, 0),
+                                                la_args(r, b.q, b.g, dv, gq, n, cps, P, 1, 0, 1, nullptr, nullptr,
+                                                        h16(b.dv)),
+                                                la_args(b.k, b.q, u, dk, qu, n, cps, P, 1, 0, 0, nullptr, nullptr, h16(b.dk)),
+                                                BH, P, s)));
+  HLA_TRY((la_launch<D, 1, WalkU2>("bwd_dq", la_args(u, b.k, b.k, dq, kk, n, cps, P, 0, 1, 0, nullptr, nullptr, h16(b.dq)),
+                                   none, none, BH, P, s)));
 #undef HLA_TRY
   return hipSuccess;
 }
@@ -592,10 +618,10 @@ bool backward_supported(int n, int d, int dv, int dtype) {
   return dtype == 1 && n >= 1 && d == dv && (d == 64 || d == 128) && span < (1LL << 31);
 }
 
-size_t backward_workspace_bytes(int BH, int n, int d) {
+size_t backward_workspace_bytes(int BH, int n, int d, int grad_dtype) {
   int P, cps;
   la_plan(d, BH, n, &P, &cps);
-  return 4 * rec_bytes(BH, P, d) + 2 * vec_bytes(BH, n, d) + 256;
+  return 4 * rec_bytes(BH, P, d) + (grad_dtype == 1 ? 3 : 2) * vec_bytes(BH, n, d) + 256;
 }
 
 hipError_t launch_backward(const Bwd& b, void* workspace, hipStream_t s) {

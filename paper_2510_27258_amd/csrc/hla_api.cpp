@@ -270,35 +270,52 @@ int hla2_forward_decay(const void* q, const void* k, const void* v, float* out, 
   return ok();
 }
 
-size_t hla2_backward_workspace_bytes(int B, int H, int n, int d, int dv, int chunk, int dtype) {
+size_t hla2_backward_workspace_bytes_ex(int B, int H, int n, int d, int dv, int chunk, int dtype, int grad_dtype) {
   if (check_dims(B, H, n, d, dv, chunk, dtype, true) != HLA_OK) return 0;
   if (!hla::backward_supported(n, d, dv, dtype)) {
     fail(HLA_ERR_UNSUPPORTED, "the backward covers bf16 q/k/v with d = dv in {64, 128} (got d=%d dv=%d dtype=%d)", d,
          dv, dtype);
     return 0;
   }
-  return hla::backward_workspace_bytes(B * H, n, d);
+  if (grad_dtype != HLA_FP32 && grad_dtype != HLA_BF16) {
+    fail(HLA_ERR_INVALID, "grad_dtype must be HLA_FP32 or HLA_BF16");
+    return 0;
+  }
+  return hla::backward_workspace_bytes(B * H, n, d, grad_dtype);
 }
 
-int hla2_backward(const void* q, const void* k, const void* v, const float* g, float* dq, float* dk, float* dv,
-                  int B, int H, int n, int d, int dv_dim, int chunk, int dtype, void* workspace,
-                  size_t workspace_bytes, void* stream) {
+size_t hla2_backward_workspace_bytes(int B, int H, int n, int d, int dv, int chunk, int dtype) {
+  return hla2_backward_workspace_bytes_ex(B, H, n, d, dv, chunk, dtype, HLA_FP32);
+}
+
+int hla2_backward_ex(const void* q, const void* k, const void* v, const float* g, void* dq, void* dk, void* dv,
+                     int B, int H, int n, int d, int dv_dim, int chunk, int dtype, int grad_dtype, void* workspace,
+                     size_t workspace_bytes, void* stream) {
   int rc;
   if ((rc = check_dims(B, H, n, d, dv_dim, chunk, dtype, true)) != HLA_OK) return rc;
   if (!hla::backward_supported(n, d, dv_dim, dtype))
     return fail(HLA_ERR_UNSUPPORTED, "the backward covers bf16 q/k/v with d = dv in {64, 128} (got d=%d dv=%d dtype=%d)",
                 d, dv_dim, dtype);
+  if (grad_dtype != HLA_FP32 && grad_dtype != HLA_BF16)
+    return fail(HLA_ERR_INVALID, "grad_dtype must be HLA_FP32 or HLA_BF16");
   if ((rc = check_ptr(q, "q")) || (rc = check_ptr(k, "k")) || (rc = check_ptr(v, "v")) || (rc = check_ptr(g, "g")) ||
       (rc = check_ptr(dq, "dq")) || (rc = check_ptr(dk, "dk")) || (rc = check_ptr(dv, "dv")))
     return rc;
   const int BH = B * H;
-  const size_t need = hla::backward_workspace_bytes(BH, n, d);
+  const size_t need = hla::backward_workspace_bytes(BH, n, d, grad_dtype);
   if (!workspace || workspace_bytes < need)
     return fail(HLA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
-  hla::Bwd b{q, k, v, g, dq, dk, dv, BH, n, d, dv_dim, dtype};
+  hla::Bwd b{q, k, v, g, dq, dk, dv, BH, n, d, dv_dim, dtype, grad_dtype};
   const hipError_t e = hla::launch_backward(b, workspace, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "backward");
   return ok();
+}
+
+int hla2_backward(const void* q, const void* k, const void* v, const float* g, float* dq, float* dk, float* dv,
+                  int B, int H, int n, int d, int dv_dim, int chunk, int dtype, void* workspace,
+                  size_t workspace_bytes, void* stream) {
+  return hla2_backward_ex(q, k, v, g, dq, dk, dv, B, H, n, d, dv_dim, chunk, dtype, HLA_FP32, workspace,
+                          workspace_bytes, stream);
 }
 
 size_t ahla_workspace_bytes(int B, int H, int n, int d, int dv, int chunk, int dtype) {

@@ -216,9 +216,7 @@ def forward_decay(q, k, v, chunk, gamma, masked=True, normalized=False, eps=1e-6
     return out
 
 
-def backward(q, k, v, g, chunk=64, workspace=None):
-    """Gradients (dq, dk, dv), fp32, of the masked unnormalised second-order HLA
-    for upstream gradient g [B,H,n,dv] fp32; q, k, v [B,H,n,d] bf16."""
+def _backward(q, k, v, g, chunk, workspace, dtype):
     _qkv(q, k, v)
     if tuple(g.shape) != tuple(v.shape):
         raise ValueError(f"g must have v's shape {tuple(v.shape)}, got {tuple(g.shape)}")
@@ -227,15 +225,22 @@ def backward(q, k, v, g, chunk=64, workspace=None):
     g = g.float().contiguous()
     B, H, n, d = q.shape
     dv_dim = v.shape[-1]
-    code = _code(q)
-    dq = torch.empty(B, H, n, d, dtype=torch.float32, device=q.device)
+    code, gcode = _code(q), capi.HLA_BF16 if dtype == torch.bfloat16 else capi.HLA_FP32
+    dq = torch.empty(B, H, n, d, dtype=dtype, device=q.device)
     dk = torch.empty_like(dq)
-    dv = torch.empty(B, H, n, dv_dim, dtype=torch.float32, device=q.device)
-    workspace = _workspace(workspace, capi.hla2_backward_workspace_bytes(B, H, n, d, dv_dim, chunk, code), q.device)
-    capi.hla2_backward(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), dq.data_ptr(), dk.data_ptr(),
-                       dv.data_ptr(), B, H, n, d, dv_dim, chunk, code, workspace.data_ptr(), _ws_bytes(workspace),
-                       _stream())
+    dv = torch.empty(B, H, n, dv_dim, dtype=dtype, device=q.device)
+    workspace = _workspace(workspace, capi.hla2_backward_workspace_bytes_ex(B, H, n, d, dv_dim, chunk, code, gcode),
+                           q.device)
+    capi.hla2_backward_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                          dv.data_ptr(), B, H, n, d, dv_dim, chunk, code, gcode, workspace.data_ptr(),
+                          _ws_bytes(workspace), _stream())
     return dq, dk, dv
+
+
+def backward(q, k, v, g, chunk=64, workspace=None):
+    """Gradients (dq, dk, dv), fp32, of the masked unnormalised second-order HLA
+    for upstream gradient g [B,H,n,dv] fp32; q, k, v [B,H,n,d] bf16."""
+    return _backward(q, k, v, g, chunk, workspace, torch.float32)
 
 
 class HLA2(torch.autograd.Function):
@@ -251,8 +256,7 @@ class HLA2(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g):
         q, k, v = ctx.saved_tensors
-        dq, dk, dv = backward(q, k, v, g, ctx.chunk)
-        return dq.to(q.dtype), dk.to(k.dtype), dv.to(v.dtype), None
+        return (*_backward(q, k, v, g, ctx.chunk, None, q.dtype), None)
 
 
 def hla2_attention(q, k, v, chunk=64):

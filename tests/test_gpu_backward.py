@@ -129,3 +129,20 @@ def test_backward_errors():
         assert ei.value.code == code, (kw, ei.value.code)
     torch.cuda.synchronize()
     assert all(bool((o == 7.0).all()) for o in outs), "a rejected call wrote an output"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,segments", [(1, 0), (65, 0), (700, 1), (701, 11)])
+def test_bf16_gradients_are_the_rounded_fp32_ones(d, n, segments, monkeypatch):
+    """hla2_backward_ex with grad_dtype bf16 (the autograd function's call):
+    exactly the fp32 gradients rounded to nearest even, rows past n untouched
+    by a neighbouring head (three heads back to back)."""
+    if segments:
+        monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    q, k, v, code = gen(1, 3, n, d, d, "unit", 9)
+    qd, kd, vd = (dev(x, code).requires_grad_() for x in (q, k, v))
+    g = torch.randn(1, 3, n, d, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    got = torch.autograd.grad(hla.hla2_attention(qd, kd, vd, 64), (qd, kd, vd), g)
+    ref = hla.backward(qd.detach(), kd.detach(), vd.detach(), g)
+    for a, b in zip(got, ref):
+        assert a.dtype == torch.bfloat16 and torch.equal(a, b.to(torch.bfloat16))
