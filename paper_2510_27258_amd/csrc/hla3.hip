@@ -378,17 +378,31 @@ __global__ __launch_bounds__(kT3) void k3_walk(const T* __restrict__ q, const T*
 // 3. Add the F carry of earlier segments and normalise.  grid (nseg, BH).
 template <typename T, int C, int D, int DV>
 __global__ __launch_bounds__(kT3) void k3_fix(const T* __restrict__ q, float* __restrict__ out,
-                                              const float* __restrict__ den_in, const float* __restrict__ pre, int n,
-                                              int cps, int nseg, int normalized, float eps) {
+                                              const float* __restrict__ den_in, const float* __restrict__ rec,
+                                              int summed, int n, int cps, int nseg, int normalized, float eps) {
   using Rc = Rec3<D, DV>;
   __shared__ float Fc[D * (DV + 1)], ec[D], Qs[C * (D + 1)], inv[C];
   const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
   if (seg == 0 && !normalized) return;          // nothing to add
   const int M = (n + C - 1) / C, c0 = seg * cps, c1 = min(M, c0 + cps);
   const size_t head_tok = (size_t)bh * n;
-  const float* pr = pre + ((size_t)bh * nseg + seg) * Rc::floats;   // the brackets before this segment
-  for (int e = tid; e < D * DV; e += kT3) Fc[(e / DV) * (DV + 1) + e % DV] = pr[Rc::oF + e];
-  for (int e = tid; e < D; e += kT3) ec[e] = pr[Rc::oe + e];
+  // the brackets before this segment: their sum in record seg (summed), or
+  // summed here, 32 records' loads in flight at a time
+  const float* head = rec + (size_t)bh * nseg * Rc::floats;
+  auto carry = [&](int off) {
+    if (summed) return head[(size_t)seg * Rc::floats + off];
+    float x = 0.f;
+    for (int s0 = 0; s0 < seg; s0 += 32) {
+      float u[32];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) u[j] = s0 + j < seg ? head[(size_t)(s0 + j) * Rc::floats + off] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 32; ++j) x += u[j];
+    }
+    return x;
+  };
+  for (int e = tid; e < D * DV; e += kT3) Fc[(e / DV) * (DV + 1) + e % DV] = carry(Rc::oF + e);
+  for (int e = tid; e < D; e += kT3) ec[e] = carry(Rc::oe + e);
   for (int c = c0; c < c1; ++c) {
     const int t0 = c * C;
     for (int e = tid; e < C * D; e += kT3) {
@@ -612,6 +626,14 @@ __global__ __launch_bounds__(kT3) void k3u_walk(const T* __restrict__ q, const T
   }
 }
 
+// Segments per head up to which the fix-up sums the earlier brackets itself
+// instead of reading the running sums of a prefix launch.  At d = dv = 16 a
+// bracket is 272 floats: 29.6 -> 28.1 us with 64 segments (8 heads of 2048),
+// 22.3 -> 19.8 with 10.  With 1056 floats (d = dv = 32) 64 segments lose,
+// 52.7 -> 54.9 us.  (The walks summing their 784 moments themselves gained
+// nothing: 29.1 us.)
+constexpr int kFixSum16 = 64, kFixSum32 = 16;
+
 template <typename T, int C, int D, int DV>
 hipError_t run3(const Fwd& f, float* recs, float* pre, float* den, int P, int cps, hipStream_t s) {
   using Rc = Rec3<D, DV>;
@@ -640,12 +662,16 @@ hipError_t run3(const Fwd& f, float* recs, float* pre, float* den, int P, int cp
   HLA_LAUNCH((k3_walk<T, C, D, DV>), grid, dim3(kT3), 0, s, q, k, v, f.out, den, recs, pre, f.n, cps, P);
   prof_stop(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  prof_start("hla3_prefix", s);
-  HLA_LAUNCH((k3_prefix<D, DV>), dim3((nbr + kT3 - 1) / kT3, f.BH), dim3(kT3), 0, s, recs, pre, P, (int)Rc::oF, nbr);
-  prof_stop(s);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const bool summed = P > (D == 16 && DV == 16 ? kFixSum16 : kFixSum32);
+  if (summed) {
+    prof_start("hla3_prefix", s);
+    HLA_LAUNCH((k3_prefix<D, DV>), dim3((nbr + kT3 - 1) / kT3, f.BH), dim3(kT3), 0, s, recs, pre, P, (int)Rc::oF, nbr);
+    prof_stop(s);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   prof_start("hla3_fix", s);
-  HLA_LAUNCH((k3_fix<T, C, D, DV>), grid, dim3(kT3), 0, s, q, f.out, den, pre, f.n, cps, P, f.normalized, f.eps);
+  HLA_LAUNCH((k3_fix<T, C, D, DV>), grid, dim3(kT3), 0, s, q, f.out, den, summed ? pre : recs, summed ? 1 : 0, f.n,
+             cps, P, f.normalized, f.eps);
   prof_stop(s);
   return hipGetLastError();
 }

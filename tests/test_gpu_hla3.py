@@ -137,3 +137,11 @@ def test_hla3_errors():
         hla.hla3_forward(q64, q64, q64, 32)
     assert ei.value.code == capi.HLA_ERR_UNSUPPORTED
     assert capi.hla3_workspace_bytes(1, 1, 64, 64, 64, 32, I.HLA_FP32) == 0
+
+
+@pytest.mark.parametrize("d,segments", [(16, 64), (16, 65), (32, 16), (32, 17)])
+def test_hla3_fix_sums_its_brackets(d, segments, monkeypatch):
+    """On both sides of the segment counts up to which the fix-up sums the
+    earlier brackets itself (64 at d = 16, 16 at d = 32)."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    _check(1, 2, 32 * segments - 5, d, d, 32, "scaled", seed=3)
