@@ -46,11 +46,15 @@ struct CfgLA {
   static constexpr int NCT = D / 32, NW = 2 * NCT, NT = 64 * NW;   // wave: row tile w / NCT, column tile w % NCT
   static constexpr int ST = D / 32, KC = C / 16, KD = D / 16;
   static constexpr int ld = D + kPad, ldA = C + kPad;
-  // row-major bf16 tiles: X, Y, Z each hi | lo, then A hi | lo
-  static constexpr int oXh = 0, oXl = oXh + C * ld, oYh = oXl + C * ld, oYl = oYh + C * ld;
-  static constexpr int oZh = oYl + C * ld, oZl = oZh + C * ld, oAh = oZl + C * ld, oAl = oAh + C * ldA;
+  // row-major bf16 tiles: Y, Z, X each hi | lo, then A hi | lo
+  static constexpr int oYh = 0, oYl = oYh + C * ld, oZh = oYl + C * ld, oZl = oZh + C * ld;
+  static constexpr int oXh = oZl + C * ld, oXl = oXh + C * ld, oAh = oXl + C * ld, oAl = oAh + C * ldA;
   static constexpr int n16 = oAl + C * ldA;
   static constexpr size_t bytes = (size_t)n16 * 2;
+  // the moments stage Y and Z only: with their LDS the two sets of a launch
+  // share a CU at d = 128 (46 -> 40 us, B1H8 n16384)
+  static constexpr size_t mom_bytes = (size_t)oXh * 2;
+  static_assert(D * D * 4 <= oXh * 2, "the moments' half sums fit Y and Z");
   static_assert(D * D * 2 <= n16, "state staging fits the tile region");
   static constexpr int kBlocks = 2 * bytes <= 160 * 1024 && NW <= 4 ? 2 : 1;
   static_assert(bytes <= 160 * 1024, "LDS budget");
@@ -97,12 +101,13 @@ struct Stage {
 // in one walk: A2 = X Z^T masked adds A2 Y, and the state is
 // sum (y z^T + z y^T), staged from the moments of (y, z) plus their transpose
 // (x and y exact in bf16: A2 takes the lo regions of X and Y).
-template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO = 0>
+template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO = 0, bool ZY = false>
 __device__ __forceinline__ void la_pass(
     const void* __restrict__ xp, const void* __restrict__ yp, const void* __restrict__ zp, float* __restrict__ out,
     float* __restrict__ rec, int n, int cps, int nseg, int rev, int acc_out, int tr, int scanned,
     const void* __restrict__ wp, float* __restrict__ rec2, uint16_t* __restrict__ out16, int seg, int bh) {
   using G = CfgLA<D>;
+  static_assert(!ZY || (!YF && !ZF && !TWO), "z is y: a bf16 input");
   static_assert(!TWO || (!XF && !YF && !MOM), "the paired pass keeps A2 in the lo tiles of x and y");
   // MO: the walk also forms its segment's moments sum w o^T of its own output
   // o with w (MO = 1: a further bf16 input wp, staged in the lo tile of z;
@@ -116,7 +121,7 @@ __device__ __forceinline__ void la_pass(
   uint16_t* Xl = lds + G::oXl;
   uint16_t* Yh = lds + G::oYh;
   uint16_t* Yl = lds + G::oYl;
-  uint16_t* Zh = lds + G::oZh;
+  uint16_t* Zh = ZY ? Yh : lds + G::oZh;   // ZY: z is y, staged once
   uint16_t* Zl = lds + G::oZl;
   uint16_t* Ah = lds + G::oAh;
   uint16_t* Al = lds + G::oAl;
@@ -153,7 +158,7 @@ __device__ __forceinline__ void la_pass(
   if (nt > 0) {
     if (!MOM) sx.fetch(rx, tile_of(0), tid);
     sy.fetch(ry, tile_of(0), tid);
-    sz.fetch(rz, tile_of(0), tid);
+    if (!ZY) sz.fetch(rz, tile_of(0), tid);
     if (MO == 1) sw.fetch(rw, tile_of(0), tid);
   }
   // MO: column ct of w o^T, all rows, over this wave's row tile of tokens
@@ -225,13 +230,13 @@ __device__ __forceinline__ void la_pass(
     // ---- stage 0: operands into LDS (fp32 ones split into hi | lo) ----
     if (!MOM) sx.store(Xh, Xl, ld, tid);
     sy.store(Yh, Yl, ld, tid);
-    sz.store(Zh, Zl, ld, tid);
+    if (!ZY) sz.store(Zh, Zl, ld, tid);
     if (MO == 1) sw.store(Zl, nullptr, ld, tid);
     lds_barrier();
     if (it + 1 < nt) {
       if (!MOM) sx.fetch(rx, tile_of(it + 1), tid);
       sy.fetch(ry, tile_of(it + 1), tid);
-      sz.fetch(rz, tile_of(it + 1), tid);
+      if (!ZY) sz.fetch(rz, tile_of(it + 1), tid);
       if (MO == 1) sw.fetch(rw, tile_of(it + 1), tid);
     }
 
@@ -308,9 +313,13 @@ __device__ __forceinline__ void la_pass(
     uint16_t* Oh = Xl;                       // MO: this tile's o, hi | lo
     uint16_t* Ol = MO == 1 ? Yl : Zl;
     if constexpr (MO != 0) store_N<kO>(o, Oh, Ol, ld, rt * 32, ct * 32, ln);
-    // ---- state advance: S0 += Y^T Z (column ct, all rows) ----
+    // ---- state advance: S0 += Y^T Z (column ct, all rows); moments: over this
+    // wave's row tile of tokens, the two row waves' halves added at the end
+    // (with each forming the whole sum the d = 128 moments launch took 55 us for
+    // 46, B1H8 n16384) ----
 #pragma unroll
-    for (int s = 0; s < G::KC; ++s) {
+    for (int s0 = 0; s0 < (MOM ? 2 : G::KC); ++s0) {
+      const int s = MOM ? 2 * rt + s0 : s0;
       const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16, ln);
       bf16x8 zl;
       if (ZF) zl = frag_tr<kO>(Zl, ld, ct * 32, s * 16, ln);
@@ -401,14 +410,26 @@ __device__ __forceinline__ void la_pass(
         }
     }
   }
-  if (MOM && rt == 0) {   // both row waves hold the column; row tile 0's write it
-    int col = ct * 32 + lr;
-    asm volatile("" : "+v"(col));
-    float* r = rec + ((size_t)bh * nseg + seg) * DD;
+  if (MOM) {   // the second token half through LDS ([ct][row][32], free after the loop's last barrier)
+    float* part = reinterpret_cast<float*>(lds) + ct * (D * 32);
+    if (rt == 1)
 #pragma unroll
-    for (int i = 0; i < ST; ++i)
+      for (int i = 0; i < ST; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) r[(size_t)(i * 32 + acc_row(e, lg)) * D + col] = S0[i][e];
+        for (int e = 0; e < 16; ++e) part[(i * 32 + acc_row(e, lg)) * 32 + lr] = S0[i][e];
+    lds_barrier();
+    if (rt == 0) {
+      int col = ct * 32 + lr;
+      asm volatile("" : "+v"(col));
+      float* r = rec + ((size_t)bh * nseg + seg) * DD;
+#pragma unroll
+      for (int i = 0; i < ST; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int row = i * 32 + acc_row(e, lg);
+          r[(size_t)row * D + col] = S0[i][e] + part[row * 32 + lr];
+        }
+    }
   }
 }
 
@@ -424,10 +445,11 @@ struct LaArgs {
   float* rec2;
   uint16_t* out16;   // not null: the result (out, with acc_out, plus this pass) goes here rounded to bf16
 };
-template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO = 0>
+template <int D, bool XF, bool YF, bool ZF, bool MOM, bool TWO = false, int MO = 0, bool ZY = false>
 struct LaPass {
+  static constexpr bool kMom = MOM;
   static __device__ __forceinline__ void run(const LaArgs& a, int seg, int bh) {
-    la_pass<D, XF, YF, ZF, MOM, TWO, MO>(a.xp, a.yp, a.zp, a.out, a.rec, a.n, a.cps, a.nseg, a.rev, a.acc_out, a.tr,
+    la_pass<D, XF, YF, ZF, MOM, TWO, MO, ZY>(a.xp, a.yp, a.zp, a.out, a.rec, a.n, a.cps, a.nseg, a.rev, a.acc_out, a.tr,
                                          a.scanned, a.wp, a.rec2, a.out16, seg, bh);
   }
 };
@@ -455,16 +477,19 @@ __global__ __launch_bounds__((CfgLA<D>::NT), (CfgLA<D>::kBlocks)) void k_la(LaAr
   }
 }
 
-// The segment moments of one set turned in place into their exclusive
-// prefix (rev = 0: the sum over the segments before each one, for causal
-// walks) or suffix (rev = 1: over the segments after it, for anti-causal
-// walks), so that a walk reads one record.  grid (D*D/256, BH), 64 * NPG
+// The segment moments of two sets turned in place into their exclusive
+// prefix (grid z = 0: the sum over the segments before each one, for causal
+// walks) or suffix (z = 1: over the segments after it, for anti-causal
+// walks), so that a walk reads one record.  grid (D*D/256, BH, 2), 64 * NPG
 // threads (NPG <= 16): a block owns 64 consecutive float4 of the records of
 // one head, and thread group g of it the g-th run of ceil(P / NPG)
 // consecutive segments.  The groups sum their runs, take the exclusive sum
 // of the groups before them from LDS, then rewrite their runs.
-__global__ __launch_bounds__(1024) void k_la_scan(float* __restrict__ rec, int rev, int P, int DD) {
+// (A launch a set took 4 x 8.4 us for 2 x 14.5, 16.8 MB a set.)
+__global__ __launch_bounds__(1024) void k_la_scan(float* __restrict__ causal, float* __restrict__ anti, int P, int DD) {
   __shared__ float4 part[16][64];
+  const int rev = blockIdx.z;
+  float* rec = rev ? anti : causal;
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6, npg = blockDim.x >> 6;
   const int per = (P + npg - 1) / npg, p0 = min(P, grp * per), p1 = min(P, p0 + per);
   float4* base = reinterpret_cast<float4*>(rec + (size_t)blockIdx.y * P * DD) + blockIdx.x * 64 + lane;
@@ -507,13 +532,13 @@ void la_plan(int D, int BH, int n, int* P, int* cps) {
   *P = (M + *cps - 1) / *cps;
 }
 
-// Prefix (rev: suffix) sums of one moment set, in place, when P > kScanAbove.
-hipError_t la_scan(float* rec, int rev, int BH, int P, int D, hipStream_t s) {
+// Prefix sums of one moment set and suffix sums of another, in place, when P > kScanAbove.
+hipError_t la_scan(float* causal, float* anti, int BH, int P, int D, hipStream_t s) {
   if (P <= kScanAbove) return hipSuccess;
   int npg = 1;
   while (npg < 16 && npg < P) npg *= 2;
   prof_start("bwd_scan", s);
-  HLA_LAUNCH(k_la_scan, dim3(D * D / 256, BH), dim3(64 * npg), 0, s, rec, rev, P, D * D);
+  HLA_LAUNCH(k_la_scan, dim3(D * D / 256, BH, 2), dim3(64 * npg), 0, s, causal, anti, P, D * D);
   prof_stop(s);
   return hipGetLastError();
 }
@@ -529,9 +554,11 @@ hipError_t la_launch(const char* name, const LaArgs& a0, const LaArgs& a1, const
   using G = CfgLA<D>;
   const void* kf = (const void*)k_la<D, NP, A, B, C>;
   hipError_t e;
-  if ((e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::bytes)) != hipSuccess) return e;
+  static_assert(A::kMom == B::kMom && A::kMom == C::kMom, "a launch is all moments or all walks");
+  const size_t lds = A::kMom ? G::mom_bytes : G::bytes;
+  if ((e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
   prof_start(name, s);
-  HLA_LAUNCH((k_la<D, NP, A, B, C>), dim3(P, BH, NP), dim3(G::NT), G::bytes, s, a0, a1, a2);
+  HLA_LAUNCH((k_la<D, NP, A, B, C>), dim3(P, BH, NP), dim3(G::NT), lds, s, a0, a1, a2);
   prof_stop(s);
   return hipGetLastError();
 }
@@ -576,12 +603,12 @@ hipError_t run_backward(const Bwd& b, char* ws, hipStream_t s) {
   // segments the scan turns it in place into the prefixes (k^T k, v^T r:
   // causal) or suffixes (g^T q, q^T u: anti-causal) the walks start from.
   // Passes that do not depend on each other share a launch.
-  using MomKK = LaPass<D, false, false, false, true>;
+  using MomKK = LaPass<D, false, false, false, true, false, 0, true>;
   using MomGQ = LaPass<D, false, true, false, true>;
-  using WalkR = LaPass<D, false, false, false, false, false, 1>;    // also v^T r
+  using WalkR = LaPass<D, false, false, false, false, false, 1, true>;    // y = z = k; also v^T r
   using WalkU = LaPass<D, false, true, false, false, false, 2>;     // also q^T u
   using WalkG = LaPass<D, true, false, true, false>;                       // x, z fp32: dq (first term), dv
-  using WalkU2 = LaPass<D, true, false, false, false>;                     // x fp32: dq (second term)
+  using WalkU2 = LaPass<D, true, false, false, false, false, 0, true>;     // x fp32, y = z = k: dq (second term)
   using WalkK = LaPass<D, false, false, true, false, true>;          // paired dk
   const LaArgs none{};
   // the moments k^T k (r, the second dq term) and g^T q (u; transposed for dv)
@@ -589,14 +616,12 @@ hipError_t run_backward(const Bwd& b, char* ws, hipStream_t s) {
     HLA_TRY((la_launch<D, 2, MomKK, MomGQ>("bwd_moments", la_args(b.k, b.k, b.k, nullptr, kk, n, cps, P, 0, 0, 0),
                                            la_args(b.g, b.g, b.q, nullptr, gq, n, cps, P, 0, 0, 0), none, BH, P,
                                            s)));
-  HLA_TRY(la_scan(kk, 0, BH, P, D, s));
-  HLA_TRY(la_scan(gq, 1, BH, P, D, s));
+  HLA_TRY(la_scan(kk, gq, BH, P, D, s));
   // r = LA+(q, k, k) with the v^T r moments, beside u = LA-(v, g, q) with the q^T u moments
   HLA_TRY((la_launch<D, 2, WalkR, WalkU>("bwd_ru", la_args(b.q, b.k, b.k, r, kk, n, cps, P, 0, 0, 0, b.v, vr),
                                          la_args(b.v, b.g, b.q, u, gq, n, cps, P, 1, 0, 0, nullptr, qu), none, BH,
                                          P, s)));
-  HLA_TRY(la_scan(vr, 0, BH, P, D, s));
-  HLA_TRY(la_scan(qu, 1, BH, P, D, s));
+  HLA_TRY(la_scan(vr, qu, BH, P, D, s));
   // the first dq term LA+(g, v, r), beside dv = LA-(r, q, g) (moments q^T g =
   // (g^T q)^T) and dk = LA-(k, q, u) + LA-(k, u, q) in one paired walk (state
   // sum q u^T + u q^T); then the second dq term LA+(u, k, k), added
