@@ -107,26 +107,33 @@ struct Cfg {
 // of Eq. (semidirect)); the total is converted back to G, h once (k_phi_to_state).
 
 // Rows r0 .. r0+15 of S C - Z and S m - z for one head, written to dst, dstv:
-// one wave per 16 x 16 tile on v_mfma_f32_16x16x4_f32 (fp32 products and
-// sums), S's rows in LDS (Sr [16][D+17], staged by stage() after the tile's
-// loads of C and Z from global memory have been issued).
-template <int D, int DV, typename ST>
+// NT threads, each wave 16 x 16 tiles on v_mfma_f32_16x16x4_f32 (fp32 products
+// and sums), S's rows in LDS (Sr [16][D+17], staged by stage() after the first
+// tile's loads of C and Z from global memory have been issued).
+template <int D, int DV, int NT, typename ST>
 __device__ __forceinline__ void cross_rows(const float* Sr, int r0, const float* C, const float* m, const float* Z,
                                            const float* z, float* dst, float* dstv, ST stage) {
-  constexpr int ld = D + 17;
-  const int tid = threadIdx.x, c0 = (tid >> 6) * 16, nn = tid & 15, g = (tid >> 4) & 3;
-  float y[D / 4], zt[4];
+  constexpr int ld = D + 17, NW = NT / 64, PW = DV / 16 / NW;
+  static_assert(PW * NW * 16 == DV, "column tiles over the waves");
+  const int tid = threadIdx.x, nn = tid & 15, g = (tid >> 4) & 3;
 #pragma unroll
-  for (int s = 0; s < D / 4; ++s) y[s] = C[(size_t)(4 * s + g) * DV + c0 + nn];
+  for (int p = 0; p < PW; ++p) {
+    const int c0 = ((tid >> 6) + NW * p) * 16;
+    float y[D / 4], zt[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) zt[i] = Z[(size_t)(r0 + 4 * g + i) * DV + c0 + nn];
-  stage();
-  __syncthreads();
-  f32x4c acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < D / 4; ++s) y[s] = C[(size_t)(4 * s + g) * DV + c0 + nn];
 #pragma unroll
-  for (int s = 0; s < D / 4; ++s) acc = mfma4(Sr[nn * ld + 4 * s + g], y[s], acc);
+    for (int i = 0; i < 4; ++i) zt[i] = Z[(size_t)(r0 + 4 * g + i) * DV + c0 + nn];
+    if (p == 0) {
+      stage();
+      __syncthreads();
+    }
+    f32x4c acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dst[(size_t)(r0 + 4 * g + i) * DV + c0 + nn] = acc[i] - zt[i];
+    for (int s = 0; s < D / 4; ++s) acc = mfma4(Sr[nn * ld + 4 * s + g], y[s], acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[(size_t)(r0 + 4 * g + i) * DV + c0 + nn] = acc[i] - zt[i];
+  }
   // four lanes per row of S m, in the first wave
   if (tid < 64) {
     const int row = tid >> 2, p = tid & 3;
@@ -146,12 +153,12 @@ __device__ __forceinline__ void cross_rows(const float* Sr, int r0, const float*
 // (32 heads, d = 128: one workgroup and
 // fp32 FMAs on register tiles took 36 us there and 85 us back, the row split
 // 9 and 9 us).  Each row block reads all of C, through L2.
-template <int D, int DV>
-__global__ __launch_bounds__(4 * DV) void k_state_to_phi(const float* __restrict__ state, float* __restrict__ segs,
-                                                         int nseg) {
-  constexpr int ld = D + 17, NT = 4 * DV;
+template <int D, int DV, int NT>
+__device__ __forceinline__ void state_rows_to_phi(const float* __restrict__ state, float* __restrict__ segs, int nseg,
+                                                  int r0, int bh) {
+  constexpr int ld = D + 17;
   __shared__ float Sr[16 * ld];
-  const int r0 = blockIdx.x * 16, bh = blockIdx.y, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   const float* src = state + (size_t)bh * dstate_floats(D, DV);
   float* dst = segs + ((size_t)bh * (nseg + 1) + nseg) * state_floats(D, DV);
   const float* C = src + packed_s_floats(D);
@@ -171,7 +178,26 @@ __global__ __launch_bounds__(4 * DV) void k_state_to_phi(const float* __restrict
     }
     if (tid < 16) dst[off_m(D, DV) + r0 + tid] = m[r0 + tid];
   };
-  cross_rows<D, DV>(Sr, r0, C, m, m + D, m + D + D * DV, dst + off_G(D, DV), dst + off_h(D, DV), stage);
+  cross_rows<D, DV, NT>(Sr, r0, C, m, m + D, m + D + D * DV, dst + off_G(D, DV), dst + off_h(D, DV), stage);
+}
+template <int D, int DV>
+__global__ __launch_bounds__(4 * DV) void k_state_to_phi(const float* __restrict__ state, float* __restrict__ segs,
+                                                         int nseg) {
+  state_rows_to_phi<D, DV, 4 * DV>(state, segs, nseg, blockIdx.x * 16, blockIdx.y);
+}
+// The same beside C = Q^T V and m = Q^T 1 of the tile ranges of mr (the K^T V
+// moments, with q for k): grid columns 0 .. nmom-1 the ranges, then the rows.
+// Neither needs the other, and a launch each took 9 and 13 us (32 heads, n =
+// 4096, d = 128) for 17.
+template <int C, int D, int DV>
+__global__ __launch_bounds__(kThreads) void k_prefill_pre(const float* __restrict__ state,
+                                                          const uint16_t* __restrict__ q,
+                                                          const uint16_t* __restrict__ v, float* __restrict__ segs,
+                                                          int n, int cps, int nseg, MomRange mr, int nmom) {
+  if ((int)blockIdx.x < nmom)
+    moments<C, D, DV, true, false, true>(q, q, v, segs, n, cps, nseg, 1, 0.f, mr, blockIdx.x, blockIdx.y);
+  else
+    state_rows_to_phi<D, DV, kThreads>(state, segs, nseg, (blockIdx.x - nmom) * 16, blockIdx.y);
 }
 
 // C and m from the [BH][F] records total, S, Phi and eta from the records
@@ -203,17 +229,16 @@ __global__ __launch_bounds__(4 * DV) void k_phi_to_state(const float* __restrict
     }
     if (tid < 16) m[r0 + tid] = src[off_m(D, DV) + r0 + tid];
   };
-  cross_rows<D, DV>(Sr, r0, src + off_C(D, DV), src + off_m(D, DV), end + off_G(D, DV), end + off_h(D, DV), m + D,
+  cross_rows<D, DV, NT>(Sr, r0, src + off_C(D, DV), src + off_m(D, DV), end + off_G(D, DV), end + off_h(D, DV), m + D,
                     m + D + D * DV, stage);
 }
 
 // total[bh][off .. off + len): the sum of a head's converted initial state
 // (slot nseg) and its records 0 .. nseg-1, eight records' loads in flight at a
 // time.  grid (ceil(len / 1024), BH).
-__global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, size_t F, int off, int len,
-                                                 float* __restrict__ total, int nseg) {
-  const int bh = blockIdx.y;
-  size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+__device__ __forceinline__ void rec_sum_block(const float* __restrict__ rec, size_t F, int off, int len,
+                                              float* __restrict__ total, int nseg, int block, int bh) {
+  size_t p = ((size_t)block * 256 + threadIdx.x) * 4;
   if (p >= (size_t)len) return;
   p += off;
   const float* base = rec + (size_t)bh * (nseg + 1) * F + p;
@@ -229,6 +254,23 @@ __global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, 
     }
   }
   *reinterpret_cast<float4*>(total + (size_t)bh * F + p) = x;
+}
+__global__ __launch_bounds__(256) void k_rec_sum(const float* __restrict__ rec, size_t F, int off, int len,
+                                                 float* __restrict__ total, int nseg) {
+  rec_sum_block(rec, F, off, len, total, nseg, blockIdx.x, blockIdx.y);
+}
+
+// The carries and the new state's C and m in one launch of the two-pass plan:
+// the running sums of the brackets (grid columns 0 .. npre-1), and the sums of
+// the C | m slots (a launch of their own took 6 us beside 8).
+template <int D, int DV>
+__global__ __launch_bounds__(256) void k_carry_total(const float* __restrict__ rec, float* __restrict__ carry,
+                                                     float* __restrict__ total, int nseg, int npre) {
+  const size_t F = state_floats(D, DV);
+  if ((int)blockIdx.x < npre)
+    seg_prefix(rec, F, (int)off_G(D, DV), D * DV + D, 0, carry, nseg, 1.f, blockIdx.x, blockIdx.y);
+  else
+    rec_sum_block(rec, F, (int)off_C(D, DV), D * DV + D, total, nseg, blockIdx.x - npre, blockIdx.y);
 }
 
 
@@ -1143,12 +1185,11 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   int cont = state ? 1 : 0;
   hipError_t e;
   if (state) {
-    if ((e = state_to_phi<D, DV>(state, segs, P, BH, s)) != hipSuccess) return e;   // slot P
-    // C = Q^T V and m = Q^T 1 of segments 0 and P - 1 (the K^T V form, with q for k)
-    const int last = P > 1 ? c0 + (P - 2) * cps : 0;
-    prof_start("moments", s);
-    HLA_LAUNCH((k_moments<CfgWS::C, D, DV, true>), dim3(P > 1 ? 2 : 1, BH), dim3(kThreads), 0, s, q, q, v, segs, n,
-               cps, P, 1, 0.f, MomRange{last, c0, P - 1});
+    // the state into slot P; C = Q^T V and m = Q^T 1 of segments 0 and P - 1
+    const int last = P > 1 ? c0 + (P - 2) * cps : 0, nmom = P > 1 ? 2 : 1;
+    prof_start("prefill_pre", s);
+    HLA_LAUNCH((k_prefill_pre<CfgWS::C, D, DV>), dim3(nmom + D / 16, BH), dim3(kThreads), 0, s, state, q, v, segs, n,
+               cps, P, MomRange{last, c0, P - 1}, nmom);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1172,8 +1213,11 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     prof_start("seg_prefix", s);
-    HLA_LAUNCH(k_seg_prefix, seg_prefix_grid(D * DV + D, BH), dim3(256), 0, s, segs, F, (int)off_G(D, DV),
-               D * DV + D, 0, carry, P, 1.f);
+    const dim3 pg = seg_prefix_grid(D * DV + D, BH);
+    if (state)
+      HLA_LAUNCH((k_carry_total<D, DV>), dim3(2 * pg.x, BH), dim3(256), 0, s, segs, carry, total, P, (int)pg.x);
+    else
+      HLA_LAUNCH(k_seg_prefix, pg, dim3(256), 0, s, segs, F, (int)off_G(D, DV), D * DV + D, 0, carry, P, 1.f);
     prof_stop(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1187,7 +1231,7 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   prof_stop(s);
   if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
   if (state) {
-    if ((e = rec_sum(segs, F, (int)off_C(D, DV), D * DV + D, total, P, BH, s)) != hipSuccess) return e;
+    if (P == 1 && (e = rec_sum(segs, F, (int)off_C(D, DV), D * DV + D, total, P, BH, s)) != hipSuccess) return e;
     return phi_to_state<D, DV>(total, segs + (size_t)(P - 1) * F, (P + 1) * F, state, BH, s);
   }
   return hipSuccess;

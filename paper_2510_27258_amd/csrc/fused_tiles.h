@@ -228,10 +228,10 @@ __device__ __forceinline__ void store_N(const f32x16& acc, uint16_t* Xh, uint16_
 struct MomRange {
   int stride, len0, slot;
 };
-template <int C, int D, int DV, bool KV = false, bool DEC = false, bool CM = true>
-__global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                                                      const uint16_t* __restrict__ v, float* __restrict__ rec, int n,
-                                                      int cps, int nseg, int want_cm, float lg2g, MomRange mr) {
+template <int C, int D, int DV, bool KV, bool DEC, bool CM>
+__device__ __forceinline__ void moments(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                        const uint16_t* __restrict__ v, float* __restrict__ rec, int n, int cps,
+                                        int nseg, int want_cm, float lg2g, MomRange mr, int seg, int bh) {
   constexpr int DT = D / 32, VT = DV / 32, KC = C / 16;
   constexpr int nS = (DT * DT + kWaves - 1) / kWaves, nC = (DT * VT + kWaves - 1) / kWaves;
   constexpr int segQ = C * D / 8, segV = C * DV / 8;
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
   static_assert(CM || !KV, "the AHLA moments form K^T V");
   if (KV) want_cm = 1;
   if (!CM) want_cm = 0;
-  const int seg = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, l = tid & 63, lr = l & 31, lg = l >> 5;
+  const int tid = threadIdx.x, l = tid & 63, lr = l & 31, lg = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = (n + C - 1) / C, c0 = seg * mr.stride, c1 = min(M, c0 + (seg == 0 ? mr.len0 : cps));
   const rsrc_t rq = make_rsrc(q + (size_t)bh * n * D, (uint32_t)n * D * 2);
@@ -435,6 +435,13 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
   }
 }
 
+template <int C, int D, int DV, bool KV = false, bool DEC = false, bool CM = true>
+__global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                      const uint16_t* __restrict__ v, float* __restrict__ rec, int n,
+                                                      int cps, int nseg, int want_cm, float lg2g, MomRange mr) {
+  moments<C, D, DV, KV, DEC, CM>(q, k, v, rec, n, cps, nseg, want_cm, lg2g, mr, blockIdx.x, blockIdx.y);
+}
+
 // dst[bh][s][0 .. len): the exclusive running sums over a head's segments of
 // one part of the records rec[bh][0 .. nseg] (F floats each, from float `off`
 // on): x_0 = (use_init ? slot nseg : 0), x_{s+1} = rho x_s + slot s (rho: the
@@ -444,9 +451,9 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
 // records), this 10 us.  (One float a thread over four times the blocks was
 // faster for one head of 65 536 tokens, 115 against 134 us a forward, and slower
 // for 64 heads, 640 against 630 us.)  grid seg_prefix_grid(len, BH).
-__global__ __launch_bounds__(256) void k_seg_prefix(const float* __restrict__ rec, size_t F, int off, int len,
-                                                    int use_init, float* __restrict__ dst, int nseg, float rho) {
-  const int bh = blockIdx.y, p = (blockIdx.x * 256 + threadIdx.x) * 4;
+__device__ __forceinline__ void seg_prefix(const float* __restrict__ rec, size_t F, int off, int len, int use_init,
+                                           float* __restrict__ dst, int nseg, float rho, int block, int bh) {
+  const int p = (block * 256 + threadIdx.x) * 4;
   if (p >= len) return;
   const float* base = rec + (size_t)bh * (nseg + 1) * F + off + p;
   float4 x = use_init ? *reinterpret_cast<const float4*>(base + (size_t)nseg * F) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -464,6 +471,10 @@ __global__ __launch_bounds__(256) void k_seg_prefix(const float* __restrict__ re
         x.x = rho * x.x + u[j].x; x.y = rho * x.y + u[j].y; x.z = rho * x.z + u[j].z; x.w = rho * x.w + u[j].w;
       }
   }
+}
+__global__ __launch_bounds__(256) void k_seg_prefix(const float* __restrict__ rec, size_t F, int off, int len,
+                                                    int use_init, float* __restrict__ dst, int nseg, float rho) {
+  seg_prefix(rec, F, off, len, use_init, dst, nseg, rho, blockIdx.x, blockIdx.y);
 }
 inline dim3 seg_prefix_grid(int len, int BH) { return dim3((len + 1023) / 1024, BH); }
 
