@@ -133,8 +133,10 @@ def traffic_for(kernel, workload):
 
 def kernel_key(name):
     """Bench name of a library kernel from its (demangled) dispatch name."""
-    if "k_ahla_walk" in name:
+    if "k_ahla_walk" in name or "k_ahla_ws_out" in name:
         return "ahla_walk"
+    if "k_ahla_ws_first" in name:
+        return "ahla_first"
     if "k_la<" in name or "k_laI" in name:
         return "bwd_pass"
     if "k_walk_ws_first" in name:
@@ -143,7 +145,7 @@ def kernel_key(name):
         return "bracket"
     if "k_walk" in name:
         return "walk_summary" if ("true" in name or "Lb1E" in name) else "walk"
-    for key in ("k_init_convert", "k_total", "k_moments", "k_carry", "k_fix", "k_scan", "k_chunk_summary", "k_readout",
+    for key in ("k_state_to_phi", "k_phi_to_state", "k_rec_sum", "k_moments", "k_carry", "k_fix", "k_scan", "k_chunk_summary", "k_readout",
                 "k_step", "k_seg_prefix"):
         if key in name:
             return key[2:]
@@ -191,7 +193,7 @@ def ingest_counters(workload, fetch_csv, write_csv, copy_fetch_csv, copy_write_c
 
 # Sources the fused forward's kernels (moments, walk, carry, fix-up) are built
 # from: the HBM counter summary is used only while these hash as recorded.
-FORWARD_SOURCES = ("fused.hip", "fused_ws.h", "fused_tiles.h", "fused.h", "common.h", "profile.h")
+FORWARD_SOURCES = ("fused.hip", "fused_ws.h", "ws_common.h", "fused_tiles.h", "fused.h", "common.h", "profile.h")
 
 
 def source_sha():

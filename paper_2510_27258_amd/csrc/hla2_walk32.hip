@@ -23,8 +23,8 @@
 // Arithmetic as the readout of hla2_chunk.hip: Q S0, Q K^T, W K, the T products
 // and the carry product on fp64 MFMA with fp32 operands widened exactly and R
 // in fp64, T V and the state sums on fp32 MFMA.  (X needs no difference of two
-// products S C and G, so the outputs are no further from the 64-bit result:
-// @ERR@.)
+// products S C and G; the outputs are no further from the 64-bit result:
+// 3.3e-7 and 3.3e-7 at d = 64, n = 4096, 1.2e-7 for 2.1e-7 at d = 32, n = 256.)
 //
 // Against a summary, a scan and a readout a 64-token chunk (one fp32 state of
 // d^2 + 2 d^2 + 2 d floats a chunk written, read, written and read again): fp32
