@@ -524,18 +524,20 @@ hipError_t run_ahla_ws(const Fwd& f, char* ws, hipStream_t s) {
 }
 
 // Whether a call takes the two-pass plan of ahla_ws.h: d = 128, and either one
-// walk a head without a first pass, or at least four tiles a segment, or many
-// segments.  Below that its two walks and two launches between them cost more
-// than the moments, carry and fix-up launches of one walk from the P prefix
-// (us, one pass / two passes): 1 tile a segment, 16 segments, 16 heads of 1000
-// 49 / 62, 4 heads 40 / 44; 3 tiles, 36 heads of 1000 60 / 67, 128 of 400
-// 62 / 70; but 7 tiles, 128 heads of 1000 122 / 113; 47 segments, 4 heads of 3000
+// walk a head without a first pass, or at least five tiles a segment (three
+// when normalised: the fix-up of one pass also divides), or many segments.
+// Below that its two walks and two launches between them cost more than the
+// moments, carry and fix-up launches of one walk from the P prefix (us, one
+// pass / two passes): 1 tile a segment, 16 segments, 16 heads of 1000 tokens
+// 49 / 62, 4 heads 40 / 44; 3 tiles, 36 heads of 1000 60 / 67 (normalised
+// 75 / 75), 128 of 400 62 / 70 (91 / 79); 4 tiles, 36 heads of 1900 86 / 90
+// (112 / 99); 5 tiles, 102 / 101 with 2400; 47 segments, 4 heads of 3000
 // 63 / 57; one walk, 128 heads of 100 tokens 36 / 14.
-bool ahla_two_pass(int BH, int n, int d) {
+bool ahla_two_pass(int BH, int n, int d, int normalized) {
   if (d != CfgAW::D) return false;
   int P, cps, c0;
   ws_plan(BH, n, &P, &cps, &c0);
-  return P == 1 || cps >= 4 || P > 24;
+  return P == 1 || cps >= (normalized ? 3 : 5) || P > 24;
 }
 
 }  // namespace
@@ -547,20 +549,24 @@ bool ahla_supported(int n, int d, int dv, int chunk, int dtype) {
 }
 
 size_t ahla_workspace_bytes(int BH, int n, int d) {
-  int P, cps;
-  if (ahla_two_pass(BH, n, d)) {
-    int c0;
+  // the plan depends on the normalized flag, which is no argument here
+  int P, cps, c0;
+  size_t two = 0, one = 0;
+  if (ahla_two_pass(BH, n, d, 0) || ahla_two_pass(BH, n, d, 1)) {
     ws_plan(BH, n, &P, &cps, &c0);
-    return ahla_ws_bytes(BH, P, d) + 256;
+    two = ahla_ws_bytes(BH, P, d) + 256;
   }
-  ahla_plan(d, BH, n, &P, &cps);
-  return records_bytes_ah(BH, P, d) + den_bytes_ah(BH, n, d) + 2 * carry_bytes_ah(BH, P, d) + 256;
+  if (!ahla_two_pass(BH, n, d, 0) || !ahla_two_pass(BH, n, d, 1)) {
+    ahla_plan(d, BH, n, &P, &cps);
+    one = records_bytes_ah(BH, P, d) + den_bytes_ah(BH, n, d) + 2 * carry_bytes_ah(BH, P, d) + 256;
+  }
+  return one > two ? one : two;
 }
 
 hipError_t launch_ahla(const Fwd& f, void* workspace, hipStream_t s) {
   if (!ahla_supported(f.n, f.d, f.dv, f.chunk, f.dtype)) return hipErrorNotSupported;
   char* ws = static_cast<char*>(workspace);
-  if (ahla_two_pass(f.BH, f.n, f.d)) return run_ahla_ws(f, ws, s);
+  if (ahla_two_pass(f.BH, f.n, f.d, f.normalized)) return run_ahla_ws(f, ws, s);
   int P, cps;
   ahla_plan(f.d, f.BH, f.n, &P, &cps);
   return f.d == 64 ? run_ahla<64>(f, ws, P, cps, s) : run_ahla<128>(f, ws, P, cps, s);

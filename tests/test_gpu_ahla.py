@@ -127,8 +127,8 @@ def test_ahla_errors():
 
 
 @pytest.mark.parametrize("n,segments,normalized", [
-    (1, 0, 0), (64, 0, 1), (193, 4, 1), (1500, 5, 0), (1500, 5, 1), (1700, 27, 1), (901, 0, 1),
-    (3600, 14, 0)])     # unnormalised: too few rows keep a denominator away from 0 at this length
+    (1, 0, 0), (64, 0, 1), (193, 4, 1), (1500, 5, 0), (1500, 5, 1), (700, 4, 0), (700, 4, 1), (1700, 27, 1),
+    (901, 0, 1), (4600, 14, 0)])     # unnormalised: too few rows keep a denominator away from 0 at this length
 def test_ahla_two_pass_d128(n, segments, normalized, monkeypatch):
     """d = 128: one output walk, one pass (193), the two passes with the
     prefixes summed by the bracket launch (up to 12 segments) and by their own
