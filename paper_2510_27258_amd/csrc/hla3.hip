@@ -401,32 +401,53 @@ __global__ __launch_bounds__(kT3) void k3_fix(const T* __restrict__ q, float* __
     }
     return x;
   };
+  // the tile's q and earlier outputs are loaded ahead of the sums they wait with
+  constexpr int NQ = (C * D + kT3 - 1) / kT3, NO = (C * DV + kT3 - 1) / kT3;
+  float qr[NQ], prev[NO];
+  auto fetch = [&](int c) {
+    const int t0 = c * C;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int e = tid + kT3 * i;
+      qr[i] = e < C * D && t0 + e / D < n ? ld3(q, (head_tok + t0 + e / D) * D + e % D) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      const int e = tid + kT3 * i;
+      prev[i] = e < C * DV && t0 + e / DV < n ? out[(head_tok + t0 + e / DV) * DV + e % DV] : 0.f;
+    }
+  };
+  if (c0 < c1) fetch(c0);
   for (int e = tid; e < D * DV; e += kT3) Fc[(e / DV) * (DV + 1) + e % DV] = carry(Rc::oF + e);
-  for (int e = tid; e < D; e += kT3) ec[e] = carry(Rc::oe + e);
+  if (normalized)
+    for (int e = tid; e < D; e += kT3) ec[e] = carry(Rc::oe + e);
   for (int c = c0; c < c1; ++c) {
     const int t0 = c * C;
-    for (int e = tid; e < C * D; e += kT3) {
-      const int t = e / D, a = e % D;
-      Qs[t * (D + 1) + a] = (t0 + t < n) ? ld3(q, (head_tok + t0 + t) * D + a) : 0.f;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int e = tid + kT3 * i;
+      if (e < C * D) Qs[(e / D) * (D + 1) + e % D] = qr[i];
     }
     __syncthreads();
-    if (normalized)
+    if (normalized) {
       for (int t = tid; t < C; t += kT3) {
         double s = 0.0;
         for (int a = 0; a < D; ++a) s += (double)Qs[t * (D + 1) + a] * ec[a];
         inv[t] = (t0 + t < n) ? 1.f / (den_in[head_tok + t0 + t] + (float)s + eps) : 0.f;
       }
-    __syncthreads();
-    for (int e = tid; e < C * DV; e += kT3) {
-      const int t = e / DV, b = e % DV;
-      if (t0 + t >= n) continue;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      const int e = tid + kT3 * i, t = e / DV, b = e % DV;
+      if (e >= C * DV || t0 + t >= n) continue;
       double s = 0.0;
       for (int a = 0; a < D; ++a) s += (double)Qs[t * (D + 1) + a] * Fc[a * (DV + 1) + b];
-      const size_t o = (head_tok + t0 + t) * DV + b;
-      float y = out[o] + (float)s;
+      float y = prev[i] + (float)s;
       if (normalized) y *= inv[t];
-      out[o] = y;
+      out[(head_tok + t0 + t) * DV + b] = y;
     }
+    if (c + 1 < c1) fetch(c + 1);
     __syncthreads();
   }
 }
