@@ -54,7 +54,6 @@ struct CfgLA {
   // the moments stage Y and Z only: with their LDS the two sets of a launch
   // share a CU at d = 128 (46 -> 40 us, B1H8 n16384)
   static constexpr size_t mom_bytes = (size_t)oXh * 2;
-  static_assert(D * D * 4 <= oXh * 2, "the moments' half sums fit Y and Z");
   static_assert(D * D * 2 <= n16, "state staging fits the tile region");
   static constexpr int kBlocks = 2 * bytes <= 160 * 1024 && NW <= 4 ? 2 : 1;
   static_assert(bytes <= 160 * 1024, "LDS budget");
@@ -138,6 +137,8 @@ __device__ __forceinline__ void la_pass(
   // ---- state: zero for the moments; else the moments of the segments
   // before (after) this one, which k_la_scan has summed into this segment's
   // record ----
+  constexpr int SR = MOM ? ST / 2 : ST;    // row tiles of the state this wave holds, from tile i0 on
+  const int i0 = MOM ? rt * SR : 0;
   f32x16 S0[ST];
 #pragma unroll
   for (int i = 0; i < ST; ++i) S0[i] = zero16();
@@ -313,22 +314,23 @@ __device__ __forceinline__ void la_pass(
     uint16_t* Oh = Xl;                       // MO: this tile's o, hi | lo
     uint16_t* Ol = MO == 1 ? Yl : Zl;
     if constexpr (MO != 0) store_N<kO>(o, Oh, Ol, ld, rt * 32, ct * 32, ln);
-    // ---- state advance: S0 += Y^T Z (column ct, all rows); moments: over this
-    // wave's row tile of tokens, the two row waves' halves added at the end
-    // (with each forming the whole sum the d = 128 moments launch took 55 us for
-    // 46, B1H8 n16384) ----
+    // ---- state advance: S0 += Y^T Z (column ct, all rows; moments: the rows of
+    // this wave's half, so that each sum runs over the tokens in order in one
+    // wave, as the walks' do.  With each row wave forming all rows the d = 128
+    // moments launch took 55 us, B1H8 n16384; with each summing half of the
+    // tokens for 46, but the sums, and so the rounded gradients, came out
+    // otherwise) ----
 #pragma unroll
-    for (int s0 = 0; s0 < (MOM ? 2 : G::KC); ++s0) {
-      const int s = MOM ? 2 * rt + s0 : s0;
+    for (int s = 0; s < G::KC; ++s) {
       const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16, ln);
       bf16x8 zl;
       if (ZF) zl = frag_tr<kO>(Zl, ld, ct * 32, s * 16, ln);
 #pragma unroll
-      for (int i = 0; i < ST; ++i) {
-        const bf16x8 yh = frag_tr<kO>(Yh, ld, i * 32, s * 16, ln);
+      for (int i = 0; i < SR; ++i) {
+        const bf16x8 yh = frag_tr<kO>(Yh, ld, (i0 + i) * 32, s * 16, ln);
         S0[i] = mfma(yh, zh, S0[i]);
         if (ZF) S0[i] = mfma(yh, zl, S0[i]);
-        if (YF) S0[i] = mfma(frag_tr<kO>(Yl, ld, i * 32, s * 16, ln), zh, S0[i]);
+        if (YF) S0[i] = mfma(frag_tr<kO>(Yl, ld, (i0 + i) * 32, s * 16, ln), zh, S0[i]);
       }
       if constexpr (TWO) {                // + Z^T Y
         const bf16x8 yb = frag_tr<kO>(Yh, ld, ct * 32, s * 16, ln);
@@ -410,26 +412,14 @@ __device__ __forceinline__ void la_pass(
         }
     }
   }
-  if (MOM) {   // the second token half through LDS ([ct][row][32], free after the loop's last barrier)
-    float* part = reinterpret_cast<float*>(lds) + ct * (D * 32);
-    if (rt == 1)
+  if (MOM) {
+    int col = ct * 32 + lr;
+    asm volatile("" : "+v"(col));
+    float* r = rec + ((size_t)bh * nseg + seg) * DD;
 #pragma unroll
-      for (int i = 0; i < ST; ++i)
+    for (int i = 0; i < SR; ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part[(i * 32 + acc_row(e, lg)) * 32 + lr] = S0[i][e];
-    lds_barrier();
-    if (rt == 0) {
-      int col = ct * 32 + lr;
-      asm volatile("" : "+v"(col));
-      float* r = rec + ((size_t)bh * nseg + seg) * DD;
-#pragma unroll
-      for (int i = 0; i < ST; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = i * 32 + acc_row(e, lg);
-          r[(size_t)row * D + col] = S0[i][e] + part[row * 32 + lr];
-        }
-    }
+      for (int e = 0; e < 16; ++e) r[(size_t)((i0 + i) * 32 + acc_row(e, lg)) * D + col] = S0[i][e];
   }
 }
 

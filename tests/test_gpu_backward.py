@@ -146,3 +146,26 @@ def test_bf16_gradients_are_the_rounded_fp32_ones(d, n, segments, monkeypatch):
     ref = hla.backward(qd.detach(), kd.detach(), vd.detach(), g)
     for a, b in zip(got, ref):
         assert a.dtype == torch.bfloat16 and torch.equal(a, b.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_moment_sums_run_over_the_tokens_in_order(d, monkeypatch):
+    """The first segment's k^T k holds +2^24 (token 0), -2^24 (token 32) and 1
+    (token 64) at rows a, b: summed in the order of the tokens that is exactly
+    1, while in fp32 2^24 + 1 is 2^24, so that sums over part of the tokens,
+    added at the end, give 0.  dv of the second segment's first token reads
+    it: q = e_a there, and q = e_b, g = e_0 at the next token, so
+    dv = (S q)_b e_0 (every other product of that row is zero)."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", "2")
+    n, a, b = 256, 1, d - 1
+    q, k, v = (torch.zeros(1, 1, n, d, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    g = torch.zeros(1, 1, n, d, device="cuda")
+    for t, x, y in ((0, 4096, 4096), (32, 4096, -4096), (64, 1, 1)):
+        k[0, 0, t, a], k[0, 0, t, b] = x, y
+    q[0, 0, 128, a] = q[0, 0, 129, b] = g[0, 0, 129, 0] = 1
+    want = torch.zeros(1, 1, n, d, device="cuda")
+    want[0, 0, 128, 0] = 1
+    want[0, 0, 129, 0] = 2.0 ** 25 + 1        # (S q)_b of q = e_b, token 129 itself
+    _, _, dv = hla.backward(q, k, v, g)
+    assert dv[0, 0, 128, 0].item() == 1.0
+    assert torch.allclose(dv, want, rtol=2.0 ** -16, atol=0)
