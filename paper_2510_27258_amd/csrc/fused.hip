@@ -1182,7 +1182,6 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   float* den = f.normalized ? f.den_out : nullptr;
   int n = f.n, normalized = f.normalized;
   float eps = f.eps;
-  int cont = state ? 1 : 0;
   hipError_t e;
   if (state) {
     // the state into slot P; C = Q^T V and m = Q^T 1 of segments 0 and P - 1
@@ -1195,8 +1194,9 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   }
   if (P > 1) {
     prof_start("walk_first", s);
-    void* a1[] = {&q, &k, &v, &out, &den, &segs, &n, &c0, &cps, &P, &cont, &normalized, &eps};
-    e = launch_ws((const void*)k_walk_ws_first, dim3(P - 1, BH), s, a1);
+    void* a1[] = {&q, &k, &v, &out, &den, &segs, &n, &c0, &cps, &P, &normalized, &eps};
+    e = launch_ws(state ? (const void*)k_walk_ws_first<true> : (const void*)k_walk_ws_first<false>, dim3(P - 1, BH),
+                  s, a1);
     prof_stop(s);
     if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
     // the S prefixes of segments 1 .. P-1 and the brackets of 1 .. P-2 (no
@@ -1227,7 +1227,8 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   prof_start("walk", s);
   float* fin = state ? segs : nullptr;
   void* a2[] = {&q, &k, &v, &out, &den, &sp, &cp, &fin, &n, &c0, &cps, &P, &seg0, &normalized, &eps};
-  e = launch_ws((const void*)k_walk_ws_out, dim3(P > 1 ? P - 1 : 1, BH), s, a2);
+  e = launch_ws(state ? (const void*)k_walk_ws_out<true> : (const void*)k_walk_ws_out<false>,
+                dim3(P > 1 ? P - 1 : 1, BH), s, a2);
   prof_stop(s);
   if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
   if (state) {

@@ -447,13 +447,17 @@ __device__ __forceinline__ void walk_ws(uint16_t* lds,
 }
 
 // First launch of the two-pass plan, grid (P - 1, BH): segment 0's output
-// walk (from the initial state in slot nseg with cont, else from zero) and the
+// walk (from the initial state in slot nseg with CONT, else from zero) and the
 // summary walks of segments 1 .. P-2 (zero state), each writing its record
-// rec[bh][seg].
+// rec[bh][seg].  CONT and FIN (below) are template arguments: with the state
+// loads and stores in the forward's kernels too, both went from 236 and 252
+// registers to 256 with two spilled, 2-4 us a call (1x200x2000 tokens, one
+// walk a head, 170 -> 174 us).
+template <bool CONT>
 __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_first(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ out, float* __restrict__ den_out, float* __restrict__ rec, int n, int c0, int cps,
-    int nseg, int cont, int normalized, float eps) {
+    int nseg, int normalized, float eps) {
   extern __shared__ __align__(16) uint16_t lds[];
   constexpr int D = CfgWS::D, DV = CfgWS::DV;
   int seg, bh;
@@ -461,7 +465,7 @@ __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_first(
   int cb, nt;
   ws_range(seg, c0, cps, (n + CfgWS::C - 1) / CfgWS::C, cb, nt);
   float* r = rec + ((size_t)bh * (nseg + 1) + seg) * state_floats(D, DV);
-  const float* init = cont ? rec + ((size_t)bh * (nseg + 1) + nseg) * state_floats(D, DV) : nullptr;
+  const float* init = CONT ? rec + ((size_t)bh * (nseg + 1) + nseg) * state_floats(D, DV) : nullptr;
   if (seg == 0)
     walk_ws<false>(lds, q, k, v, out, den_out, init, init ? init + off_G(D, DV) : nullptr, r, bh, n, cb, nt,
                    normalized, eps);
@@ -472,9 +476,10 @@ __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_first(
 // Output walks from the true carries, grid (walks, BH): grid column x walks
 // segment seg0 + x.  spre: [BH][nseg][D*D] S prefixes and carry:
 // [BH][nseg][D*DV + D] Phi, eta carries (both null for a single segment).
-// fin: null, or the records: a single segment then starts from the initial
+// FIN: fin holds the records; a single segment then starts from the initial
 // state in slot nseg, and the last segment's walk writes its ending S, Phi
 // and eta into record nseg - 1.
+template <bool FIN>
 __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_out(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ out, float* __restrict__ den_out, const float* __restrict__ spre,
@@ -490,7 +495,7 @@ __global__ __launch_bounds__(CfgWS::NT, 1) void k_walk_ws_out(
   const float* si = spre ? spre + ((size_t)bh * nseg + seg) * D * D : nullptr;
   const float* ci = carry ? carry + ((size_t)bh * nseg + seg) * (D * DV + D) : nullptr;
   float* r = nullptr;
-  if (fin && seg == nseg - 1) {
+  if (FIN && seg == nseg - 1) {
     r = fin + ((size_t)bh * (nseg + 1) + seg) * state_floats(D, DV);
     if (!spre) {                     // one segment: slot 1 holds the initial state
       si = r + state_floats(D, DV);
