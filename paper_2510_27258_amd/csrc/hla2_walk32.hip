@@ -22,9 +22,18 @@
 //
 // Arithmetic as the readout of hla2_chunk.hip: Q S0, Q K^T, W K, the T products
 // and the carry product on fp64 MFMA with fp32 operands widened exactly and R
-// in fp64, T V and the state sums on fp32 MFMA.  (X needs no difference of two
-// products S C and G; the outputs are no further from the 64-bit result:
-// 3.3e-7 and 3.3e-7 at d = 64, n = 4096, 1.2e-7 for 2.1e-7 at d = 32, n = 256.)
+// in fp64, T V and the state sums on fp32 MFMA.  Each tile's part of S0, X0 and
+// y is formed from zero and added to the running state once, so a state sees
+// one rounding at its own size a tile (accumulated into the running state
+// itself, four tokens an MFMA, one segment of 4096 tokens was 2-6 times
+// further off).  Distance from the 64-bit result, the chunked kernels' (one
+// rounding a 64-token chunk) and this: 3.3e-7 and 1.5e-7 at d = 64, n = 4096
+// in 22 segments; with one segment a head, masked, d = 128, n = 4096 3.3e-7 and
+// 2.3e-7, n = 16384 5.7e-7 and 3.9e-7 (X needs no difference of two products
+// S C and G).  Unmasked, C is the same sum in both: in one segment of 4096
+// tokens 2.6e-7 and 2.7e-7, of 16384 3.9e-7 and 4.8e-7, so unmasked segments
+// are bounded (kMaxTiles): 2.0e-7 and 2.9e-7.  Up to 64 tokens, one chunk,
+// 0.7-1.0e-7 and 0.8-1.2e-7: one fp32 rounding of the state more.
 //
 // Against a summary, a scan and a readout a 64-token chunk (one fp32 state of
 // d^2 + 2 d^2 + 2 d floats a chunk written, read, written and read again): fp32
@@ -40,6 +49,7 @@
 // 16 x 16 accumulator tiles.  Element i of lane (g, n) is row 4 g + i, so with
 // the contraction index of step (kt, i) taken as 16 kt + 4 g + i a state tile
 // is its own B operand, and an A operand's four steps are one 16-byte read.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 
@@ -54,6 +64,11 @@ namespace {
 
 constexpr int kTile = 32;
 constexpr int kSelfSum = 8;
+// Tiles of the longest unmasked segment (2048 tokens), whatever the head count.
+// Where this cuts a head, it is cut into enough segments for four rounds of
+// the chip at least, so that a last round which is partly empty costs little:
+// fp32 1x160x4096, d = 128, one segment 2118 us, two 2741, seven 2008.
+constexpr int kMaxTiles = 64;
 
 template <int D>
 struct GW {
@@ -164,12 +179,14 @@ __device__ __forceinline__ void add_outer(f32x4c* st, const float* Y, const floa
   for (int rt = 0; rt < NW; ++rt) {
     float x[8];
     column8<D>(x, Y, 16 * rt + nn, g);
+    f32x4c t = {0.f, 0.f, 0.f, 0.f};
     if constexpr (sizeof(T) == 2) {
-      st[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pack8(x), pack8(z), st[rt], 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pack8(x), pack8(z), t, 0, 0, 0);
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) st[rt] = mfma4(x[j], z[j], st[rt]);
+      for (int j = 0; j < 8; ++j) t = mfma4(x[j], z[j], t);
     }
+    st[rt] += t;
   }
 }
 
@@ -215,8 +232,10 @@ __global__ __launch_bounds__(4 * D) void k_gmoments(const T* __restrict__ q, con
     if (CM) {
       column8<D>(z, Vs, col, g);
       add_outer<T, D>(X, Qs, z, nn, g);
+      float yt = 0.f;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) y += Qs[((tid & 3) * 8 + j) * G::ldq + (tid >> 2)];
+      for (int j = 0; j < 8; ++j) yt += Qs[((tid & 3) * 8 + j) * G::ldq + (tid >> 2)];
+      y += yt;
     }
     lds_barrier();
   }
@@ -435,10 +454,11 @@ __global__ __launch_bounds__(4 * D, D == 128 ? 2 : 3) void k_gwalk(
     column8<D>(vb, Vs, col, g);
     if constexpr (MASKED) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int t = 16 * (j >> 2) + 4 * g + (j & 3);
+      for (int rt = 0; rt < NW; ++rt) {
+        f32x4c x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int rt = 0; rt < NW; ++rt) X[rt] = mfma4((float)R[t * ldr + 16 * rt + nn], vb[j], X[rt]);
+        for (int j = 0; j < 8; ++j) x = mfma4((float)R[(16 * (j >> 2) + 4 * g + (j & 3)) * ldr + 16 * rt + nn], vb[j], x);
+        X[rt] += x;
       }
     } else {
       add_outer<T, D>(X, Qs, vb, nn, g);
@@ -584,6 +604,8 @@ hipError_t run(const Fwd& f, float* ws, size_t ws_bytes, hipStream_t s) {
   const int M = (f.n + kTile - 1) / kTile, BH = f.BH, n = f.n;
   // enough segments to fill the chip, as many as the workspace holds
   int P = 256 * G::kBlocks / BH;
+  if (!f.masked && M > kMaxTiles * std::max(P, 1))
+    P = std::max((M + kMaxTiles - 1) / kMaxTiles, (4 * 256 * G::kBlocks + BH - 1) / BH);
   if (const char* e = getenv("HLA_FUSED_SEGMENTS")) P = atoi(e);
   P = P < 1 ? 1 : P > M ? M : P;
   while (P > 1 && 4 * ws_floats(BH, n, D, P, f.masked, f.normalized) > ws_bytes) --P;

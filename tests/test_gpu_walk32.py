@@ -37,3 +37,36 @@ def test_walk32(d, n, segments, masked, normalized, monkeypatch):
             assert rowwise_err(out[good], (num / (den + eps)[..., None])[good]) <= 1e-5
         else:
             assert rowwise_err(out, num) <= 1e-5
+
+
+def _distance(out, ref):
+    return float(np.linalg.norm(out - ref) / np.linalg.norm(ref))
+
+
+@pytest.mark.parametrize("masked", [1, 0])
+@pytest.mark.parametrize("d", [64, 128])
+def test_walk32_one_long_segment_keeps_its_precision(d, masked, monkeypatch):
+    """4096 fp32 tokens in one segment.  A running state takes one rounding at
+    its own size a tile, 128 in all: relative to its end (a sum of products of
+    either sign grows as the root of the tokens) sqrt(128 / 2) times about
+    0.4 * 2^-24 each, for S and for X 2.7e-7 together, and half of that again is
+    allowed.  Eight roundings a tile come to 8e-7 by the same count."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", "1")
+    q, k, v, code = gen(1, 2, 4096, d, d, "scaled", 17)
+    num, _, _, _ = native.hla2_serial_c(q, k, v, masked=bool(masked), threads=2)
+    out = hla.forward(dev(q, code), dev(k, code), dev(v, code), 64, masked=bool(masked),
+                      algo=capi.HLA_ALGO_CHUNKED).cpu().numpy()
+    assert _distance(out, num) <= 4e-7
+
+
+def test_walk32_bounds_unmasked_segments():
+    """Unmasked, 140 equal heads of 16384 tokens at d = 128: by the head count
+    one segment each, whose 512 tile sums come to 5.4e-7 (twice sqrt(512 / 2)
+    0.4 * 2^-24, added in squares); segments of at most 2048 tokens keep the
+    running sums of a segment and of the records below half of that each."""
+    q, k, v, code = gen(1, 1, 16384, 128, 128, "scaled", 19)
+    num, _, _, _ = native.hla2_serial_c(q, k, v, masked=False, threads=1)
+    heads = [dev(x, code).expand(1, 140, -1, -1).contiguous() for x in (q, k, v)]
+    out = hla.forward(*heads, 64, masked=False, algo=capi.HLA_ALGO_CHUNKED)
+    assert bool((out == out[:, :1]).all())
+    assert _distance(out[:, 0].cpu().numpy(), num[:, 0]) <= 4e-7
