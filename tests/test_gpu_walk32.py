@@ -39,6 +39,43 @@ def test_walk32(d, n, segments, masked, normalized, monkeypatch):
             assert rowwise_err(out, num) <= 1e-5
 
 
+def _plan(n, d, BH, segments, chunk, masked, normalized):
+    """(P, cps): the segments of the walk and their 32-token tiles for a requested count, cut to what the workspace
+    (two arrays of the general path's chunk states) holds."""
+    M, F, chunks = -(-n // 32), 2 * d * d + d, -(-n // min(chunk, 64))
+    room = 2 * (-(-BH * chunks * (3 * d * d + 2 * d) * 4 // 256) * 256)
+    P = min(segments, M)
+    while P > 1 and 4 * ((2 if P > 8 else 1) * BH * P * F + (BH * n if masked and normalized else 0)) > room:
+        P -= 1
+    cps = -(-M // P)
+    return -(-M // cps), cps
+
+
+@pytest.mark.parametrize("masked,normalized", [(1, 0), (1, 1), (0, 0), (0, 1)])
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("n,segments,plan", [(2040, 8, (8, 8)), (2015, 9, (9, 7)), (2101, 22, (22, 3)),
+                                             (1120, 18, (18, 2))])
+def test_walk32_segments_of_several_tiles(d, n, segments, plan, masked, normalized, monkeypatch):
+    """On both sides of the eight segments up to which the walk and the fix-up
+    sum the records themselves; more than the sixteen records of one round of
+    the running sums, their last round partly empty; segments of an odd number
+    of tiles (the fix-up takes two a workgroup from d = 64 on).  fp32 inputs."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    B, H, chunk, eps = 1, 2, 16, 1e-6
+    assert _plan(n, d, B * H, segments, chunk, masked, normalized) == plan
+    q, k, v, code = gen(B, H, n, d, d, "scaled", 13)
+    print(f"walk32 d={d} n={n} segments={segments} masked={masked} normalized={normalized}", flush=True)
+    num, den, _, _ = native.hla2_serial_c(q, k, v, masked=bool(masked), threads=8)
+    out = hla.forward(dev(q, code), dev(k, code), dev(v, code), chunk, masked=bool(masked),
+                      normalized=bool(normalized), eps=eps, algo=capi.HLA_ALGO_CHUNKED).cpu().numpy()
+    assert np.isfinite(out).all()
+    if normalized:
+        good = np.abs(den + eps) >= 0.05 * O.hla2_den_scale(q, k, masked=bool(masked))
+        assert rowwise_err(out[good], (num / (den + eps)[..., None])[good]) <= 1e-5
+    else:
+        assert rowwise_err(out, num) <= 1e-5
+
+
 def _distance(out, ref):
     return float(np.linalg.norm(out - ref) / np.linalg.norm(ref))
 
