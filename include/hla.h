@@ -112,7 +112,9 @@ int hla2_forward(const void *q, const void *k, const void *v, float *out,
  * denominator output.  den: NULL, or (normalized = 1 only) fp32 [B, H, n]
  * receiving den_t of Thm. 1 (q_t^T (S_t m_t - h_t) masked, q_t^T S_t m_t
  * unmasked), without eps; den != NULL with normalized = 0 is HLA_ERR_INVALID.
- * HLA_ALGO_FUSED returns HLA_ERR_UNSUPPORTED for shapes it does not cover. */
+ * HLA_ALGO_FUSED returns HLA_ERR_UNSUPPORTED for shapes it does not cover.
+ * Sizes for HLA_ALGO_AUTO are those of the masked operator; unmasked it takes
+ * HLA_ALGO_CHUNKED, whose size the caller then asks for. */
 size_t hla2_workspace_bytes_ex(int B, int H, int n, int d, int dv, int chunk, int dtype, int algo);
 int hla2_forward_ex(const void *q, const void *k, const void *v, float *out, float *den,
                     int B, int H, int n, int d, int dv, int chunk, int masked, int normalized,

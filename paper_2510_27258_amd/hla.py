@@ -139,7 +139,9 @@ def forward(q, k, v, chunk, masked=True, normalized=False, eps=1e-6, algo=capi.H
     out = _fp32_out(out, (B, H, n, dv), q.device)
     if den is not None:
         den = _fp32_out(den, (B, H, n), q.device, "den")
-    workspace = _workspace(workspace, capi.hla2_workspace_bytes_ex(B, H, n, d, dv, chunk, code, algo), q.device)
+    # HLA_ALGO_AUTO's size is the masked operator's; unmasked it takes the chunked algorithm
+    sized = capi.HLA_ALGO_CHUNKED if algo == capi.HLA_ALGO_AUTO and not masked else algo
+    workspace = _workspace(workspace, capi.hla2_workspace_bytes_ex(B, H, n, d, dv, chunk, code, sized), q.device)
     capi.hla2_forward_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                          den.data_ptr() if den is not None else None, B, H, n, d, dv, chunk,
                          int(masked), int(normalized), float(eps), code, workspace.data_ptr(),

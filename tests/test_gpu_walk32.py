@@ -107,3 +107,16 @@ def test_walk32_bounds_unmasked_segments():
     out = hla.forward(*heads, 64, masked=False, algo=capi.HLA_ALGO_CHUNKED)
     assert bool((out == out[:, :1]).all())
     assert _distance(out[:, 0].cpu().numpy(), num[:, 0]) <= 4e-7
+
+
+@pytest.mark.parametrize("d,dv,chunk", [(64, 64, 64), (128, 128, 128), (64, 32, 64), (16, 16, 16)])
+def test_unmasked_by_default_algorithm(d, dv, chunk):
+    """hla.forward(masked=False) without an algorithm on bf16: the workspace it
+    allocates is the chunked algorithm's, which the unmasked operator takes
+    (at the first three shapes the masked operator takes the fused one)."""
+    q, k, v, code = gen(1, 2, 300, d, dv, "unit", 23)
+    x = [dev(t, code) for t in (q, k, v)]
+    num, _, _, _ = native.hla2_serial_c(q, k, v, masked=False, threads=2)
+    out = hla.forward(*x, chunk, masked=False)
+    assert (out == hla.forward(*x, chunk, masked=False, algo=capi.HLA_ALGO_CHUNKED)).all()
+    assert rowwise_err(out.cpu().numpy(), num) <= 1e-5
