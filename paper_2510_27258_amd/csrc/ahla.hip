@@ -507,9 +507,9 @@ hipError_t run_ahla_ws(const Fwd& f, char* ws, hipStream_t s) {
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     prof_start("ahla_bracket", s);
-    HLA_LAUNCH((k_ws_bracket<D, DV, true>), dim3(P - 1, BH), dim3(1024), 0, s, segs, ppre, P, summed);
+    e = ws_bracket<D, DV, true>(segs, ppre, P, BH, summed, s);
     prof_stop(s);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (e != hipSuccess) return e;
     prof_start("ahla_prefix", s);
     HLA_LAUNCH(k_seg_prefix, seg_prefix_grid(D * DV + D, BH), dim3(256), 0, s, segs, state_floats(D, DV),
                (int)off_G(D, DV), D * DV + D, 0, carry, P, 1.f);

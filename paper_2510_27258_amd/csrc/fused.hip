@@ -1209,9 +1209,9 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     prof_start("bracket", s);
-    HLA_LAUNCH((k_ws_bracket<D, DV>), dim3(P - 1, BH), dim3(1024), 0, s, segs, spre, P, summed);
+    e = ws_bracket<D, DV, false>(segs, spre, P, BH, summed, s);
     prof_stop(s);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (e != hipSuccess) return e;
     prof_start("seg_prefix", s);
     const dim3 pg = seg_prefix_grid(D * DV + D, BH);
     if (state)

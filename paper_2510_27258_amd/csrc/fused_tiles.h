@@ -446,7 +446,8 @@ __global__ __launch_bounds__(kThreads) void k_moments(const uint16_t* __restrict
 // one part of the records rec[bh][0 .. nseg] (F floats each, from float `off`
 // on): x_0 = (use_init ? slot nseg : 0), x_{s+1} = rho x_s + slot s (rho: the
 // decay of one segment's moments over the next, 1 without decay).  Each walk
-// then reads its segment's prefix as one record.  Eight records' loads in
+// then reads its segment's prefix as one record (the last record is in no
+// prefix and is not read).  Eight records' loads in
 // flight: one load after another took 20 us for 61 segments of 4 heads (64 KB
 // records), this 10 us.  (One float a thread over four times the blocks was
 // faster for one head of 65 536 tokens, 115 against 134 us a forward, and slower
@@ -463,7 +464,7 @@ __device__ __forceinline__ void seg_prefix(const float* __restrict__ rec, size_t
     float4 u[B];
 #pragma unroll
     for (int j = 0; j < B; ++j)
-      u[j] = s + j < nseg ? *reinterpret_cast<const float4*>(base + (size_t)(s + j) * F) : make_float4(0.f, 0.f, 0.f, 0.f);
+      u[j] = s + j < nseg - 1 ? *reinterpret_cast<const float4*>(base + (size_t)(s + j) * F) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int j = 0; j < B; ++j)
       if (s + j < nseg) {

@@ -7,6 +7,7 @@
 #include <cstdlib>
 
 #include "fused_tiles.h"
+#include "profile.h"
 
 namespace hla {
 namespace {
@@ -73,12 +74,18 @@ inline void ws_plan(int BH, int n, int* P, int* cps, int* c0) {
 
 // Segments per head up to which the bracket launch sums the prefixes itself;
 // above it k_seg_prefix writes them first.  A bracket workgroup reads every
-// earlier record, P^2 / 2 of them a head in chains of P / 2 loads: 45 us with
-// 61 segments (4 heads of 30 000 tokens) against 10 us for the launch and 17 us
-// for the brackets after it.  At 9 segments (32 heads, two prefills of about
-// 4000 tokens) the extra launch costs 2 % (333 against 326 us), and so it does
-// at 5 (64 heads of 16 384: 658 against 650 us).
-constexpr int kBracketSumMax = 12;
+// earlier record, P^2 / 2 of them a head in chains of P / 4 rounds, against one
+// more launch.  With itself / with the launch, us a forward: 13 segments (20
+// heads of 4000 tokens) 90.7 / 93.2, 17 (16 heads of 4000) 83.3 / 84.6 (AHLA, 16
+// heads of 6000, 104.0 / 106.7), 22 (12 heads of 6000) 99.3 / 90.4, 33 (8 heads of
+// 6000) 82.4 / 78.6, 52 (5 heads of 6000) 86.4 / 68.1.
+constexpr int kBracketSumMax = 17;
+// (segment, head) pairs up to which two workgroups share a bracket: 14 pairs (2
+// heads of 500 tokens) 34.7 -> 30.9 us a forward, 60 (4 heads of 1000) 43.8 ->
+// 41.1, 124 (4 heads of 2000) 47.5 -> 46.1.  With more than half of the chip's
+// CUs at work two only add reads: 156 pairs (4 heads of 2500) 50.4 -> 51.3, 240
+// (24 heads of 4000) 100.6 -> 106.1.
+constexpr int kBracketSplitMax = 128;
 
 // The prefixes and the brackets of the two-pass plan (Eq. semidirect in the
 // Phi form).  For segment s = 1 .. nseg-1: S_{<s}, the sum of the S
@@ -91,85 +98,100 @@ constexpr int kBracketSumMax = 12;
 // n in G | h; the prefixes are those of (P, m^K) ([D DV | D] in spre[s]) and
 // the bracket is (E_s + (K^T Q)_s P_{<s}, n_s + (K^T Q)_s m_{<s}) (Eq.
 // AHLA-semidirect).
-// grid (nseg - 1, BH), 1024 threads, one workgroup per (segment, head), a
-// head's workgroups on one XCD.  S_{<s} and C_s are split into three bf16
-// pieces (24 bits: the fp32 values) in LDS, one half of the contraction at a
-// time, and wave w forms the 32 x 32 tile (w / 4, w % 4) of S_{<s} C_s from
-// the six products of at least 2^-16 with fp32 accumulation: the bracket is
-// what the later segments' carries are summed from, and with two pieces
+// grid (HALVES (nseg - 1), BH), 1024 / HALVES threads: HALVES workgroups a
+// (segment, head), each one part of the prefix (rows of S_{<s}; AH: columns of
+// P_{<s}) and of the bracket, a head's workgroups on one XCD.  S_{<s} and C_s are
+// split into three bf16 pieces (24 bits: the fp32 values) in LDS, 32 steps of
+// the contraction at a time, and each wave forms one 32 x 32 tile of S_{<s} C_s
+// from the six products of at least 2^-16 with fp32 accumulation: the bracket
+// is what the later segments' carries are summed from, and with two pieces
 // (three products) it was the larger part of their error (prefill of 8000
-// tokens on 32 heads, outputs 4.3-4.7e-6 from the 64-bit result, now 2.9e-6).  The
-// loads bound it: 1 MB a workgroup at 8 segments.
-template <int D, int DV, bool AH = false>
-__global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, float* __restrict__ spre, int nseg,
-                                                     int summed) {
-  constexpr int KH = D / 2, ldS = KH + kPad, ldC = DV + 16, NT = 1024;   // ldC: C is read through the transpose unit
-  static_assert(D == 128 && DV == 128, "16 waves of 32 x 32 output tiles");
-  __shared__ __align__(16) uint16_t Sp[3][D * ldS], Cp[3][KH * ldC];
+// tokens on 32 heads, outputs 4.3-4.7e-6 from the 64-bit result, now 2.9e-6).
+// The third piece costs about 1 us a forward where all CUs are at work (with
+// two pieces / now: 32 heads of 4000 tokens 114.2 / 115.8 us, 16 of 2000 66.8 /
+// 67.5, 64 of 1000 77.0 / 78.4).  Slabs of 64, or 8 waves of two tiles each, are
+// no faster.
+template <int D, int DV, bool AH, int HALVES>
+__global__ __launch_bounds__(1024 / HALVES, 4) void k_ws_bracket(float* __restrict__ rec, float* __restrict__ spre,
+                                                                 int nseg, int summed) {
+  static_assert(D == 128 && DV == 128, "16 waves of 32 x 32 tiles a bracket");
+  constexpr int KH = 32, NT = 1024 / HALVES, NK = D / KH;             // slabs of the contraction
+  constexpr int RL = AH ? D : D / HALVES, CR = AH ? DV / HALVES : DV;    // rows of the left, columns of the right operand
+  constexpr int LQ = KH / 4, RQ = CR / 4;                                // float4 a row of their slabs
+  constexpr int LS = NT / LQ, RS = NT / RQ, NL = RL / LS, NR = KH / RS;  // rows at a time; float4 a thread and slab
+  constexpr int ldS = KH + kPad, ldC = CR + 16;                          // ldC: read through the transpose unit
+  constexpr int NP = NK * (AH ? NR : NL), NO = NK * (AH ? NL : NR);      // float4 a thread: prefix part, own operand
+  __shared__ __align__(16) uint16_t Sp[3][RL * ldS], Cp[3][KH * ldC];
   __shared__ float mv[D], ep[D];
   int s, bh;
   seg_head(s, bh);
-  s += 1;
+  const int half = s % HALVES;
+  s = 1 + s / HALVES;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lr = l & 31, lg = l >> 5;
-  const int r0 = 32 * (w >> 2), c0 = 32 * (w & 3);
+  const int r0 = 32 * (w / (CR / 32)), c0 = 32 * (w % (CR / 32));
   const size_t F = state_floats(D, DV);
   float* r = rec + ((size_t)bh * (nseg + 1) + s) * F;
-  constexpr int NS4 = D * D / 4 / NT;
-  // the segment's own C (AH: K^T Q) and Phi first (the last segment's record
-  // is not read: it has no bracket)
+  // piece i of a thread: NL of a slab of the left operand (KH of its columns), NR
+  // of a slab of the right one (KH of its rows), so that every lane has its
+  // share of each slab
+  const int lrow = tid / LQ, lcol = (tid % LQ) * 4, rrow = tid / RQ, rcol = (tid % RQ) * 4;
+  auto at_left = [&](int i) { return (lrow + LS * (i % NL) + (AH ? 0 : RL * half)) * D + KH * (i / NL) + lcol; };
+  auto at_right = [&](int i) { return (rrow + RS * i) * DV + rcol + (AH ? CR * half : 0); };
+  auto at_pre = [&](int i) { return AH ? at_right(i) : at_left(i); };
+  auto at_own = [&](int i) { return AH ? at_left(i) : at_right(i); };
+  constexpr size_t oPre = AH ? (size_t)D * D : 0, oOwn = AH ? 0 : (size_t)D * D;   // S at 0, C at D D
+  // the segment's own operand first (the last segment's record is not read: it has no bracket)
   const bool own = s < nseg - 1;
-  float4 sx[NS4], cx[NS4];     // the left and the right operand
-  float4* mine = AH ? sx : cx;
-  float4* pre = AH ? cx : sx;
-  constexpr size_t oPre = AH ? (size_t)D * D : 0, oMine = AH ? 0 : (size_t)D * D;   // S at 0, C at D D
-  f32x16 acc;        // b_s: element e is row r0 + acc_row(e, lg), column c0 + lr
-  float eta = 0.f, m = 0.f;
+  float4 ox[NO], px[NP];
   if (own) {
 #pragma unroll
-    for (int i = 0; i < NS4; ++i) mine[i] = reinterpret_cast<const float4*>(r + oMine)[tid + NT * i];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = r[off_G(D, DV) + (size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr];
-    if (tid < D) {
-      eta = r[off_h(D, DV) + tid];
-      if (!AH) m = r[off_m(D, DV) + tid];
-    }
+    for (int i = 0; i < NO; ++i) ox[i] = *reinterpret_cast<const float4*>(r + oOwn + at_own(i));
   }
   // the prefix: already in spre (summed), or the earlier records' S (AH: C)
-  // slots, two records' loads in flight at a time
-#pragma unroll
-  for (int i = 0; i < NS4; ++i) pre[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  const float* r0s = rec + (size_t)bh * (nseg + 1) * F + oPre;
-  for (int j0 = 0; j0 < (summed ? 0 : s); j0 += 2) {
-    float4 u[2][NS4];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < NS4; ++i)
-        u[j][i] = j0 + j < s ? reinterpret_cast<const float4*>(r0s + (size_t)(j0 + j) * F)[tid + NT * i]
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < NS4; ++i) {
-        pre[i].x += u[j][i].x; pre[i].y += u[j][i].y; pre[i].z += u[j][i].z; pre[i].w += u[j][i].w;
-      }
-  }
+  // slots, four records' loads in flight at a time
+  float m = !AH && own && tid < D ? r[off_m(D, DV) + tid] : 0.f;
   float* sp = spre + ((size_t)bh * nseg + s) * (AH ? D * DV + D : D * D);
   if (summed) {
     if (!own) return;
 #pragma unroll
-    for (int i = 0; i < NS4; ++i) pre[i] = reinterpret_cast<const float4*>(sp)[tid + NT * i];
+    for (int i = 0; i < NP; ++i) px[i] = *reinterpret_cast<const float4*>(sp + at_pre(i));
     if (AH && tid < D) m = sp[D * DV + tid];
   } else {
+    const float* r0s = rec + (size_t)bh * (nseg + 1) * F + oPre;
 #pragma unroll
-    for (int i = 0; i < NS4; ++i) reinterpret_cast<float4*>(sp)[tid + NT * i] = pre[i];
+    for (int i = 0; i < NP; ++i) px[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j0 = 0; j0 < s; j0 += 4) {
+      float4 u[4][NP];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+          u[j][i] = j0 + j < s ? *reinterpret_cast<const float4*>(r0s + (size_t)(j0 + j) * F + at_pre(i))
+                               : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          px[i].x += u[j][i].x; px[i].y += u[j][i].y; px[i].z += u[j][i].z; px[i].w += u[j][i].w;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) *reinterpret_cast<float4*>(sp + at_pre(i)) = px[i];
     if (AH && tid < D) {
 #pragma unroll 4
       for (int j = 0; j < s; ++j) m += r0s[(size_t)j * F + D * DV + tid];
-      sp[D * DV + tid] = m;
+      if (half == 0) sp[D * DV + tid] = m;
     }
   }
   if (!own) return;
+  float* out = r + off_G(D, DV) + (AH ? CR * half : RL * half * DV);
+  f32x16 acc;        // the bracket: element e is row r0 + acc_row(e, lg), column c0 + lr
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = out[(size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr];
+  // eta (AH: n) of this part's rows (AH: all rows, by part 0)
+  const int er = (AH ? 0 : RL * half) + tid;
+  const bool eown = tid < RL && (!AH || half == 0);
+  const float eta = eown ? r[off_h(D, DV) + er] : 0.f;
   if (tid < D) mv[tid] = m;
   auto put = [](uint16_t* p0, uint16_t* p1, uint16_t* p2, const float4& x) {
     uint32_t h0, h1, m0, m1, l0, l1;
@@ -179,20 +201,18 @@ __global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, fl
     *reinterpret_cast<uint2*>(p1) = make_uint2(m0, m1);
     *reinterpret_cast<uint2*>(p2) = make_uint2(l0, l1);
   };
-  const int row = tid / (D / 4), col = 4 * (tid % (D / 4));   // of piece 0; piece i is 32 rows further down
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < NK; ++h) {
     if (h) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NS4; ++i)
-      if (col / KH == h) {
-        const int o = (row + 32 * i) * ldS + col - KH * h;
-        put(Sp[0] + o, Sp[1] + o, Sp[2] + o, sx[i]);
-      }
+    for (int i = 0; i < NL; ++i) {
+      const int o = (lrow + LS * i) * ldS + lcol;
+      put(Sp[0] + o, Sp[1] + o, Sp[2] + o, AH ? ox[NL * h + i] : px[NL * h + i]);
+    }
 #pragma unroll
-    for (int i = 0; i < NS4 / 2; ++i) {
-      const int o = (row + 32 * i) * ldC + col;
-      put(Cp[0] + o, Cp[1] + o, Cp[2] + o, cx[i + NS4 / 2 * h]);
+    for (int i = 0; i < NR; ++i) {
+      const int o = (rrow + RS * i) * ldC + rcol;
+      put(Cp[0] + o, Cp[1] + o, Cp[2] + o, AH ? px[NR * h + i] : ox[NR * h + i]);
     }
     __syncthreads();
 #pragma unroll
@@ -211,18 +231,32 @@ __global__ __launch_bounds__(1024) void k_ws_bracket(float* __restrict__ rec, fl
       acc = mfma(a[2], b[0], acc);
     }
   }
-  // the left operand times m from the registers: 32 lanes hold a row
+  // the left operand times m from the registers: LQ lanes hold a row
 #pragma unroll
-  for (int i = 0; i < NS4; ++i) {
-    float x = sx[i].x * mv[col] + sx[i].y * mv[col + 1] + sx[i].z * mv[col + 2] + sx[i].w * mv[col + 3];
+  for (int i = 0; i < NL; ++i) {
+    float x = 0.f;
 #pragma unroll
-    for (int o = 1; o < 32; o <<= 1) x += __shfl_xor(x, o);
-    if (col == 0) ep[row + 32 * i] = x;
+    for (int h = 0; h < NK; ++h) {
+      const float4 v = AH ? ox[NL * h + i] : px[NL * h + i];
+      const float* y = mv + KH * h + lcol;
+      x += v.x * y[0] + v.y * y[1] + v.z * y[2] + v.w * y[3];
+    }
+#pragma unroll
+    for (int o = 1; o < LQ; o <<= 1) x += __shfl_xor(x, o);
+    if (lcol == 0) ep[lrow + LS * i] = x;
   }
 #pragma unroll
-  for (int e = 0; e < 16; ++e) r[off_G(D, DV) + (size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr] = acc[e];
+  for (int e = 0; e < 16; ++e) out[(size_t)(r0 + acc_row(e, lg)) * DV + c0 + lr] = acc[e];
   __syncthreads();
-  if (tid < D) r[off_h(D, DV) + tid] = eta + ep[tid];
+  if (eown) r[off_h(D, DV) + er] = eta + ep[tid];
+}
+template <int D, int DV, bool AH>
+hipError_t ws_bracket(float* rec, float* spre, int nseg, int BH, int summed, hipStream_t s) {
+  if (BH * (nseg - 1) <= kBracketSplitMax)
+    HLA_LAUNCH((k_ws_bracket<D, DV, AH, 2>), dim3(2 * (nseg - 1), BH), dim3(512), 0, s, rec, spre, nseg, summed);
+  else
+    HLA_LAUNCH((k_ws_bracket<D, DV, AH, 1>), dim3(nseg - 1, BH), dim3(1024), 0, s, rec, spre, nseg, summed);
+  return hipGetLastError();
 }
 
 }  // namespace
