@@ -479,7 +479,7 @@ hipError_t run_ahla_ws(const Fwd& f, char* ws, hipStream_t s) {
   constexpr int D = CfgAW::D, DV = CfgAW::DV;
   const int BH = f.BH;
   int P, cps, c0;
-  ws_plan(BH, f.n, &P, &cps, &c0);
+  ws_plan(BH, f.n, kAhlaSummaryRatio, &P, &cps, &c0);
   float* segs = reinterpret_cast<float*>(ws);
   float* ppre = reinterpret_cast<float*>(ws + records_bytes_ah(BH, P, D));
   float* carry = ppre + (size_t)BH * P * (D * DV + D);
@@ -525,19 +525,28 @@ hipError_t run_ahla_ws(const Fwd& f, char* ws, hipStream_t s) {
 
 // Whether a call takes the two-pass plan of ahla_ws.h: d = 128, and either one
 // walk a head without a first pass, or at least five tiles a segment (three
-// when normalised: the fix-up of one pass also divides), or many segments.
-// Below that its two walks and two launches between them cost more than the
-// moments, carry and fix-up launches of one walk from the P prefix (us, one
-// pass / two passes): 1 tile a segment, 16 segments, 16 heads of 1000 tokens
-// 49 / 62, 4 heads 40 / 44; 3 tiles, 36 heads of 1000 60 / 67 (normalised
-// 75 / 75), 128 of 400 62 / 70 (91 / 79); 4 tiles, 36 heads of 1900 86 / 90
-// (112 / 99); 5 tiles, 102 / 101 with 2400; 47 segments, 4 heads of 3000
-// 63 / 57; one walk, 128 heads of 100 tokens 36 / 14.
+// when normalised: the fix-up of one pass also divides), or many segments,
+// whose chain of prefixes one pass reads in every walk.  Below that its two
+// walks and two launches between them cost more than the moments, carry and
+// fix-up launches of one walk from the P prefix (us, one pass / two passes):
+//   one walk, 128 heads of 100 tokens 36 / 14
+//   one tile a segment: 16 segments (16 heads of 1000) 48 / 58, 27 (9 heads of
+//     1700) 50 / 57, 41 (6 heads of 2600) 56 / 61, 49 (5 heads of 3100) 60 / 62;
+//     47 on 4 heads of 3000 55 / 55, on 3 52 / 51, on 1 48 / 45, 79 on 2 heads of
+//     5000 67 / 59, 250 on 1 of 16 000 150 / 102
+//   two tiles: 28 segments (8 heads of 3500) 62 / 64 (normalised 72 / 70), 32 (6
+//     heads of 4000) 61 / 60, 40 (5 heads of 5000) 65 / 62; 24 normalised (10
+//     heads of 3000) 72 / 71
+//   three: 8 segments (36 heads of 1000) 60 / 67 (normalised 75 / 75), 24 (10 heads
+//     of 4500) 75 / 73; four: 8 (36 heads of 1900) 86 / 90 (112 / 99), 28 (8 heads
+//     of 7000) 88 / 81; five: 102 / 101 with 36 heads of 2400.
 bool ahla_two_pass(int BH, int n, int d, int normalized) {
   if (d != CfgAW::D) return false;
   int P, cps, c0;
-  ws_plan(BH, n, &P, &cps, &c0);
-  return P == 1 || cps >= (normalized ? 3 : 5) || P > 24;
+  ws_plan(BH, n, kAhlaSummaryRatio, &P, &cps, &c0);
+  if (P == 1 || cps >= (normalized ? 3 : 5)) return true;
+  if (cps == 1) return P > 46 && BH <= 4;
+  return P > (cps == 2 && !normalized ? 31 : 23);
 }
 
 }  // namespace
@@ -553,7 +562,7 @@ size_t ahla_workspace_bytes(int BH, int n, int d) {
   int P, cps, c0;
   size_t two = 0, one = 0;
   if (ahla_two_pass(BH, n, d, 0) || ahla_two_pass(BH, n, d, 1)) {
-    ws_plan(BH, n, &P, &cps, &c0);
+    ws_plan(BH, n, kAhlaSummaryRatio, &P, &cps, &c0);
     two = ahla_ws_bytes(BH, P, d) + 256;
   }
   if (!ahla_two_pass(BH, n, d, 0) || !ahla_two_pass(BH, n, d, 1)) {

@@ -1170,7 +1170,7 @@ hipError_t run_ws(const Fwd& f, float* state, float* total, char* ws, hipStream_
   constexpr int D = CfgWS::D, DV = CfgWS::DV;
   const int BH = f.BH;
   int P, cps, c0;
-  ws_plan(BH, f.n, &P, &cps, &c0);
+  ws_plan(BH, f.n, kWsSummaryRatio, &P, &cps, &c0);
   const size_t F = state_floats(D, DV);
   float* segs = reinterpret_cast<float*>(ws);
   float* spre = reinterpret_cast<float*>(ws + records_bytes(BH, P, D, DV));
@@ -1343,7 +1343,7 @@ bool fused_plan_query(int BH, int n, int d, int dv, int chunk, int* P, int* tile
   if (!sh) return false;
   int cps, c0;
   if (ws_shape(*sh) && !legacy_pipeline()) {
-    ws_plan(BH, n, P, &cps, &c0);   // the plan of the forward without states
+    ws_plan(BH, n, kWsSummaryRatio, P, &cps, &c0);   // the plan of the forward, and of prefill where it writes outputs
   } else {
     fused_plan(*sh, BH, n, P, &cps);
     c0 = cps;
@@ -1373,7 +1373,7 @@ size_t fused_workspace_bytes(int BH, int n, int d, int dv, int chunk) {
   const size_t legacy = legacy_ws_bytes(BH, n, P, sh->C, d, dv);
   if (ws_shape(*sh)) {
     int Pw, cw, c0;
-    ws_plan(BH, n, &Pw, &cw, &c0);
+    ws_plan(BH, n, kWsSummaryRatio, &Pw, &cw, &c0);
     const size_t w = ws_pipeline_bytes(BH, Pw);
     return w > legacy ? w : legacy;
   }

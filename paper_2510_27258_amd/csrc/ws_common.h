@@ -37,20 +37,22 @@ __device__ __forceinline__ void read_ahead() {
   }
 }
 
-// Per-tile time of the summary walk over that of the output walk (both at
-// one workgroup per CU, d = dv = 128: about 3.9 and 6.6 us per tile).
-constexpr double kWsSummaryRatio = 0.65;
+// Per-tile time of the summary walk over that of the output walk, both at one
+// workgroup per CU: second order about 3.9 and 6.6 us per tile, of which 0.65
+// measured best (0.5 to 1 were tried); AHLA (us at 0.55 / 0.65 / 0.75 / 0.85) 64 heads of
+// 8000 tokens 317 / 311 / 311 / 310, of 3000 144 / 144 / 138 / 142, 100 of 4000
+// 257 / 250 / 241 / 253, 16 of 8000 123 / 121 / 120 / 120.
+constexpr double kWsSummaryRatio = 0.65, kAhlaSummaryRatio = 0.75;
 
 // Segments of the two-pass plan: with Q = 256 / BH walks per head in each
 // launch (one workgroup per CU), segments 1 .. P-1 get x tiles each (the
 // last the rest) and segment 0 about r x, r the ratio above, so that segment
 // 0's output walk and the summary walks beside it end together.  With fewer
 // than two later segments the plan is a single output walk per head.
-inline void ws_plan(int BH, int n, int* P, int* cps, int* c0) {
+inline void ws_plan(int BH, int n, double r, int* P, int* cps, int* c0) {
   const int M = (n + kWsTile - 1) / kWsTile;
   int Q = 256 / BH;
   if (const char* e = getenv("HLA_FUSED_SEGMENTS")) Q = atoi(e) - 1;
-  double r = kWsSummaryRatio;
   if (const char* e = getenv("HLA_WS_RATIO")) r = atof(e);
   if (Q >= 2 && M >= 3 && r > 0.0) {
     int x = (int)ceil(M / (Q + r));

@@ -130,9 +130,9 @@ def test_ahla_errors():
     (1, 0, 0), (64, 0, 1), (193, 4, 1), (1500, 5, 0), (1500, 5, 1), (700, 4, 0), (700, 4, 1), (1700, 27, 1),
     (901, 0, 1), (4600, 14, 0)])     # unnormalised: too few rows keep a denominator away from 0 at this length
 def test_ahla_two_pass_d128(n, segments, normalized, monkeypatch):
-    """d = 128: one output walk, one pass (193), the two passes with the
-    prefixes summed by the bracket launch (up to 12 segments) and by their own
-    (more), many segments, ragged tails."""
+    """d = 128, ragged tails: one output walk, one pass (193; 1700 and 901, in
+    14 and 15 segments of one or two tiles), two passes.  test_gpu_two_pass.py
+    holds every branch of the two passes, with its plan."""
     if segments:
         monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
     _check(1, 3, n, 128, 128, normalized=bool(normalized), seed=21)
@@ -140,7 +140,8 @@ def test_ahla_two_pass_d128(n, segments, normalized, monkeypatch):
 
 @pytest.mark.parametrize("segments", [13, 24])
 def test_forward_two_pass_many_segments(segments, monkeypatch):
-    """The second-order walk at d = 128 with the S prefixes from their own launch."""
+    """The second-order walk at d = 128 in 11 and 16 segments (what the plan
+    makes of the counts asked for)."""
     monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
     q, k, v, code = gen(1, 2, 1900, 128, 128, "unit", 5)
     num, _, _, _ = native.hla2_serial_c(q, k, v, masked=True, threads=4)

@@ -23,12 +23,12 @@ BAR = 3.6e-6
 SUM_MAX, SPLIT_MAX = 17, 128     # segments summed by the bracket launch; (segment, head) pairs of two workgroups
 
 
-def _plan(BH, n, segments):
-    """(segments, tiles of a later segment) of the plan."""
+def _plan(BH, n, segments, ratio=0.65):
+    """(segments, tiles of a later segment) of the plan; ratio: a summary tile's time over an output tile's."""
     M, Q = -(-n // 64), segments - 1 if segments else 256 // BH
     if Q >= 2 and M >= 3:
-        x = math.ceil(M / (Q + 0.65))
-        rest = M - max(1, int(0.65 * x + 0.5))
+        x = math.ceil(M / (Q + ratio))
+        rest = M - max(1, int(ratio * x + 0.5))
         if rest > 0:
             x = max(x, -(-rest // Q))
             if -(-rest // x) >= 2:
@@ -53,11 +53,11 @@ def _close(out, ref, code):
     assert off.max() <= BAR, off
 
 
-def _branch(BH, n, segments, monkeypatch):
+def _branch(BH, n, segments, monkeypatch, ratio=0.65):
     """The plan, and whether its prefixes have their own launch and a bracket two workgroups."""
     if segments:
         monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
-    P, cps = _plan(BH, n, segments)
+    P, cps = _plan(BH, n, segments, ratio)
     return P, cps, P > SUM_MAX, BH * (P - 1) <= SPLIT_MAX
 
 
@@ -78,12 +78,13 @@ def test_forward(BH, n, segments, P, cps, own_launch, split, normalized, monkeyp
 @pytest.mark.parametrize("BH,n,segments,normalized,P,cps,own_launch,split", [
     (2, 3300, 12, 0, 11, 5, False, True), (2, 3300, 12, 1, 11, 5, False, True), (3, 3600, 20, 1, 20, 3, True, True),
     (13, 2000, 12, 1, 11, 3, False, False), (17, 2900, 10, 0, 10, 5, False, False),
-    (3, 2000, 0, 0, 32, 1, True, True), (3, 2000, 0, 1, 32, 1, True, True), (6, 2000, 0, 1, 32, 1, True, False)])
+    (2, 3000, 0, 0, 47, 1, True, True), (2, 3000, 0, 1, 47, 1, True, True), (4, 3000, 0, 1, 47, 1, True, False),
+    (6, 4000, 0, 0, 32, 2, True, False), (2, 3000, 26, 1, 24, 2, True, True)])
 def test_ahla(BH, n, segments, normalized, P, cps, own_launch, split, monkeypatch):
     """Plans that take the two passes: five tiles a segment, three when
-    normalised, or more than 24 segments."""
-    assert _branch(BH, n, segments, monkeypatch) == (P, cps, own_launch, split)
-    assert cps >= (3 if normalized else 5) or P > 24
+    normalised, or many segments of one or two."""
+    assert _branch(BH, n, segments, monkeypatch, 0.75) == (P, cps, own_launch, split)
+    assert cps >= (3 if normalized else 5) or P > 46 or (cps == 2 and P > (23 if normalized else 31))
     q, k, v, code = _inputs(BH, n, normalized, 37)
     print(f"two-pass ahla BH={BH} n={n} P={P} normalized={normalized}", flush=True)
     num, den, _ = native.ahla_serial_c(q, k, v, threads=8)
