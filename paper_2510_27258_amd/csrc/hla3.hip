@@ -681,12 +681,14 @@ __global__ __launch_bounds__(kT3) void k3u_walk(const T* __restrict__ q, const T
 }
 
 // Segments per head up to which the fix-up sums the earlier brackets itself
-// instead of reading the running sums of a prefix launch.  At d = dv = 16 a
-// bracket is 272 floats: 29.6 -> 28.1 us with 64 segments (8 heads of 2048),
-// 22.3 -> 19.8 with 10.  With 1056 floats (d = dv = 32) 64 segments lose,
-// 52.7 -> 54.9 us.  (The walks summing their 784 moments themselves gained
-// nothing: 29.1 us.)
-constexpr int kFixSum16 = 64, kFixSum32 = 16;
+// instead of reading the running sums of a prefix launch (us, with the launch /
+// itself).  At d = dv = 16 a bracket is 272 floats: 32 segments 34.5 / 32.2, 64
+// (8 heads of 2048) 28.2 / 25.0, 128 35.4 / 30.7, 256 (2 heads of 8192) 50.0 / 42.3
+// (normalised, where segment 0 is fixed up too, 50.6 / 50.4), 500 78.2 / 64.9
+// (79.1 / 80.4).  Else up to 1056 floats (d = dv = 32): 16 segments 45.2 / 43.4, 32
+// (16 heads of 1024) 46.1 / 44.3, 42 48.1 / 48.0, 47 (2 heads of 1500) 37.9 / 39.5,
+// 85 52.1 / 54.0.  (The walks summing their 784 moments themselves gained nothing.)
+constexpr int kFixSum16 = 256, kFixSum32 = 32;
 
 template <typename T, int C, int D, int DV>
 hipError_t run3(const Fwd& f, float* recs, float* pre, float* den, int P, int cps, hipStream_t s) {

@@ -141,7 +141,15 @@ def test_hla3_errors():
 
 @pytest.mark.parametrize("d,segments", [(16, 64), (16, 65), (32, 16), (32, 17)])
 def test_hla3_fix_sums_its_brackets(d, segments, monkeypatch):
-    """On both sides of the segment counts up to which the fix-up sums the
-    earlier brackets itself (64 at d = 16, 16 at d = 32)."""
+    """Two and three rounds of the 32 brackets that the fix-up sums at a time
+    (d = 16), half a round and one more (d = 32)."""
     monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
     _check(1, 2, 32 * segments - 5, d, d, 32, "scaled", seed=3)
+
+
+@pytest.mark.parametrize("d,segments", [(16, 256), (16, 257), (32, 32), (32, 33)])
+def test_hla3_fix_sums_or_reads_its_brackets(d, segments, monkeypatch):
+    """On both sides of the segment counts up to which the fix-up sums the
+    earlier brackets itself (256 at d = 16, 32 at d = 32), normalised too."""
+    monkeypatch.setenv("HLA_FUSED_SEGMENTS", str(segments))
+    _check(1, 2, 16 * segments - 5, d, d, 16, "scaled", normalized=segments < 64, seed=3)
