@@ -143,6 +143,12 @@ def kernel_key(name):
         return "walk_first"
     if "k_ws_bracket" in name:
         return "bracket"
+    if "k_walk_ws_out" in name:          # <true>: from and into a decode state
+        return "walk"
+    for part, key in (("k_gwalk", "walk32"), ("k_gmoments", "moments32"), ("k_gfix", "fix32"), ("k_gprefix", "prefix32"),
+                      ("k_prefill_pre", "prefill_pre"), ("k_carry_total", "carry_total")):
+        if part in name:
+            return key
     if "k_walk" in name:
         return "walk_summary" if ("true" in name or "Lb1E" in name) else "walk"
     for key in ("k_state_to_phi", "k_phi_to_state", "k_rec_sum", "k_moments", "k_carry", "k_fix", "k_scan", "k_chunk_summary", "k_readout",
@@ -193,7 +199,8 @@ def ingest_counters(workload, fetch_csv, write_csv, copy_fetch_csv, copy_write_c
 
 # Sources the fused forward's kernels (moments, walk, carry, fix-up) are built
 # from: the HBM counter summary is used only while these hash as recorded.
-FORWARD_SOURCES = ("fused.hip", "fused_ws.h", "ws_common.h", "fused_tiles.h", "fused.h", "common.h", "profile.h")
+FORWARD_SOURCES = ("fused.hip", "fused_ws.h", "ws_common.h", "fused_tiles.h", "fused.h", "mfma16.h", "common.h",
+                   "profile.h")
 
 
 def source_sha():

@@ -42,3 +42,32 @@ def test_backward_launch_bytes():
     assert bench.BWD_PASS_BYTES["bwd_ru"] == [(2 + 2 + 2 + 2 + 4) + (2 + 4 + 2 + 4)]
     assert bench.BWD_PASS_BYTES["bwd_dq_dv_dk"] == [(4 + 2 + 4 + 4) + (4 + 2 + 4 + 4) + (2 + 2 + 4 + 4)]
     assert bench.BWD_PASS_BYTES["bwd_dq"] == [4 + 2 + 2 + 8]
+
+
+def test_kernel_keys_of_dispatch_names():
+    # the counter summary's key of each kernel, from its demangled and its mangled name
+    ns = "void hla::(anonymous namespace)::"
+    for name, key in (
+            ("k_walk_ws_out<false>", "walk"), ("k_walk_ws_out<true>", "walk"), ("k_walk_ws_first<true>", "walk_first"),
+            ("k_ws_bracket<128, 128, true, 2>", "bracket"), ("k_prefill_pre<64, 128, 128>", "prefill_pre"),
+            ("k_carry_total<128, 128>", "carry_total"), ("k_carry<64, 64>", "carry"), ("k_seg_prefix", "seg_prefix"),
+            ("k_gwalk<float, 64, true>", "walk32"), ("k_gmoments<unsigned short, 128, true>", "moments32"),
+            ("k_gfix<float, 64>", "fix32"), ("k_gprefix", "prefix32"), ("k_fix<64, 64, 64, false>", "fix"),
+            ("k_walk_rs<64, false, false>", "walk"), ("k_ahla_ws_first", "ahla_first")):
+        assert bench.kernel_key(ns + name + "(float const*)") == key, name
+    assert bench.kernel_key("_ZN3hla12_GLOBAL__N_113k_walk_ws_outILb1EEEvPKt") == "walk"
+    assert bench.kernel_key("__amd_rocclr_copyBuffer") is None
+
+
+def test_forward_sources_hold_what_the_forward_includes():
+    # the hash that a counter summary is checked by covers every header that fused.hip reaches
+    import os
+    import re
+    csrc = os.path.join(bench.ROOT, "paper_2510_27258_amd", "csrc")
+    seen, todo = set(), ["fused.hip"]
+    while todo:
+        f = todo.pop()
+        if f not in seen and os.path.exists(os.path.join(csrc, f)):
+            seen.add(f)
+            todo += re.findall(r'#include "([^"/]+)"', open(os.path.join(csrc, f)).read())
+    assert seen <= set(bench.FORWARD_SOURCES), sorted(seen - set(bench.FORWARD_SOURCES))
