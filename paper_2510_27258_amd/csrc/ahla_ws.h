@@ -23,8 +23,8 @@
 // the second launch walks the outputs of segments 1 .. P-1, each row final
 // (divided) when written.  Against one walk from the P prefix (a moments
 // launch before it, a fix-up over every row after it), at one wave a SIMD
-// with both state columns, 64 heads of 8000 tokens: 429 -> 325 us (walk 316,
-// fix-up 92, moments 73 against first launch 155, outputs 190, brackets 19).
+// with both state columns, 64 heads of 8000 tokens: 431 -> 329 us, on another box 428 -> 313 (walk 316,
+// fix-up 92, moments 73 against first launch 135, outputs 178, brackets 17, sums 7).
 #pragma once
 #include "ws_common.h"
 

@@ -316,10 +316,9 @@ __device__ __forceinline__ void la_pass(
     if constexpr (MO != 0) store_N<kO>(o, Oh, Ol, ld, rt * 32, ct * 32, ln);
     // ---- state advance: S0 += Y^T Z (column ct, all rows; moments: the rows of
     // this wave's half, so that each sum runs over the tokens in order in one
-    // wave, as the walks' do.  With each row wave forming all rows the d = 128
-    // moments launch took 55 us, B1H8 n16384; with each summing half of the
-    // tokens for 46, but the sums, and so the rounded gradients, came out
-    // otherwise) ----
+    // wave, as the walks' do.  Half of the tokens each, with the halves added at
+    // the end, is another fp32 order and gave other rounded gradients; the d =
+    // 128 launch, B1H8 n16384, took 39.4 us that way and takes 38.3 this way) ----
 #pragma unroll
     for (int s = 0; s < G::KC; ++s) {
       const bf16x8 zh = frag_tr<kO>(Zh, ld, ct * 32, s * 16, ln);

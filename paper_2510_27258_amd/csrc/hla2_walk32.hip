@@ -37,13 +37,14 @@
 //
 // Against a summary, a scan and a readout a 64-token chunk (one fp32 state of
 // d^2 + 2 d^2 + 2 d floats a chunk written, read, written and read again): fp32
-// 2x16x4096, d = 64, 455 -> 163 us (walk 110, fix-up 34, moments 15, running
-// sums 2 x 7); bf16 unmasked 1x16x4001, d = 128, 675 -> 163 us (walk 138,
+// 2x16x4096, d = 64, 455 -> 163 us (walk 104, fix-up 32, moments 15, running
+// sums 2 x 7); bf16 unmasked 1x16x4001, d = 128, 675 -> 163 us (walk 131,
 // moments 25, sums 12); fp32 1x2x256, d = 32, 35 -> 19 us.
-// The fp64 MFMA bounds the walk: 2 d^2 products a token in the carry terms,
-// 3 x 24 d in the triangles (at d = 64 above, 69 of the 110 us at the rate of
-// the part, 71 TFLOP/s).  Tiles of 32 tokens keep the triangles short and the
-// LDS at 72 KB for d = 128, 36 KB for 64.
+// The largest part of the walk is fp64 MFMA: 2 d^2 products a token in the
+// carry terms and 3 x 24 d in the triangles, at the part's 71 TFLOP/s 47 of the
+// 104 us at d = 64 above (3.4 GFLOP) and 76 of the 131 at d = 128 (5.4 GFLOP).
+// For the rest all waves wait at the tile's barriers.  Tiles of 32 tokens keep
+// the triangles short and the LDS at 72 KB for d = 128, 39 KB for 64.
 //
 // Layout: D / 16 waves; wave w holds column tile w of S0 and X0, all rows, as
 // 16 x 16 accumulator tiles.  Element i of lane (g, n) is row 4 g + i, so with
@@ -81,7 +82,7 @@ struct GW {
   static constexpr size_t bytes = sizeof(float) * nf;
   static constexpr size_t F = (size_t)2 * D * D + D;      // a record: S | X | y
   static_assert(oR % 4 == 0 && oW % 4 == 0 && bytes <= 80 * 1024, "LDS layout");
-  // walks a CU, by their registers (174 to 208 at d = 128, 152 at 64).  Forcing
+  // walks a CU, by their registers (178 to 206 at d = 128, 130 to 168 at 64).  Forcing
   // 128 registers and 2 and 4 walks a CU spilled: 210 for 163 us unmasked at
   // d = 128, 182 for 163 us in fp32 at d = 64.
   static constexpr int kBlocks = D == 128 ? 1 : D == 64 ? 3 : 6;

@@ -213,8 +213,8 @@ def test_fused_d128_first_segment_length(ratio, monkeypatch):
 
 def test_fused_d128_pipelines_agree(monkeypatch):
     """The d = 128 forward's two pipelines (every output row written once
-    from the true carry, and the earlier walk + carry fix-up, which prefill
-    with states still uses) agree to the bf16 bar, num and den."""
+    from the true carry, and the earlier walk + carry fix-up, whose walk prefill
+    without outputs still uses) agree to the bf16 bar, num and den."""
     q, k, v, code = gen(2, 3, 64 * 11 + 5, 128, 128, "unit", 17)
     qd, kd, vd = dev(q, code), dev(k, code), dev(v, code)
     res = []
