@@ -26,7 +26,8 @@
 // y is formed from zero and added to the running state once, so a state sees
 // one rounding at its own size a tile (accumulated into the running state
 // itself, four tokens an MFMA, one segment of 4096 tokens was 2-6 times
-// further off).  Distance from the 64-bit result, the chunked kernels' (one
+// further off; at d = 128 that is 2 % of the time, 237.5 -> 242.5 us for fp32
+// 4x12x1290).  Distance from the 64-bit result, the chunked kernels' (one
 // rounding a 64-token chunk) and this: 3.3e-7 and 1.5e-7 at d = 64, n = 4096
 // in 22 segments; with one segment a head, masked, d = 128, n = 4096 3.3e-7 and
 // 2.3e-7, n = 16384 5.7e-7 and 3.9e-7 (X needs no difference of two products
@@ -82,7 +83,7 @@ struct GW {
   static constexpr size_t bytes = sizeof(float) * nf;
   static constexpr size_t F = (size_t)2 * D * D + D;      // a record: S | X | y
   static_assert(oR % 4 == 0 && oW % 4 == 0 && bytes <= 80 * 1024, "LDS layout");
-  // walks a CU, by their registers (178 to 206 at d = 128, 130 to 168 at 64).  Forcing
+  // walks a CU, by their registers (178 to 200 at d = 128, 130 to 168 at 64).  Forcing
   // 128 registers and 2 and 4 walks a CU spilled: 210 for 163 us unmasked at
   // d = 128, 182 for 163 us in fp32 at d = 64.
   static constexpr int kBlocks = D == 128 ? 1 : D == 64 ? 3 : 6;
@@ -454,12 +455,19 @@ __global__ __launch_bounds__(4 * D, D == 128 ? 2 : 3) void k_gwalk(
     float vb[8];
     column8<D>(vb, Vs, col, g);
     if constexpr (MASKED) {
+      constexpr int GR = D == 128 ? 4 : 1;   // row tiles side by side: fp32 1x300x2048 2285 -> 2246 us; none at d = 64
 #pragma unroll
-      for (int rt = 0; rt < NW; ++rt) {
-        f32x4c x = {0.f, 0.f, 0.f, 0.f};
+      for (int r0 = 0; r0 < NW; r0 += GR) {
+        f32x4c x[GR];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x = mfma4((float)R[(16 * (j >> 2) + 4 * g + (j & 3)) * ldr + 16 * rt + nn], vb[j], x);
-        X[rt] += x;
+        for (int r = 0; r < GR; ++r) x[r] = f32x4c{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int r = 0; r < GR; ++r)
+            x[r] = mfma4((float)R[(16 * (j >> 2) + 4 * g + (j & 3)) * ldr + 16 * (r0 + r) + nn], vb[j], x[r]);
+#pragma unroll
+        for (int r = 0; r < GR; ++r) X[r0 + r] += x[r];
       }
     } else {
       add_outer<T, D>(X, Qs, vb, nn, g);
